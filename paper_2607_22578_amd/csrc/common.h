@@ -67,19 +67,23 @@ __host__ __device__ __forceinline__ Split make_split(int64_t nu, int64_t N, int 
   if (sp.qtiles <= 0 || sp.ntiles <= 0 || grid <= 0) return sp;
   uint32_t cap = (uint32_t)(smax < sp.ntiles ? smax : sp.ntiles);
   if (cap < 1) cap = 1;
+  // 32-bit divisions (a 64-bit one takes a wave over a hundred instructions, and
+  // every kernel of the score step starts with this): qt <= 2^30 / mq, and
+  // qt * s is at most 8 * grid or qt
   const uint32_t qt = (uint32_t)sp.qtiles, nt = (uint32_t)sp.ntiles, gr = (uint32_t)grid;
   uint64_t best_cost = ~0ull;
   uint32_t best = 1;
+#pragma unroll 1
   for (uint32_t r = 1; r <= 8; ++r) {
-    uint32_t s = (uint32_t)(((uint64_t)r * gr) / qt);
+    uint32_t s = r * gr / qt;
     if (s < 1) s = 1;
     if (s > cap) s = cap;
-    const uint64_t items = (uint64_t)qt * s;
-    const uint64_t cost = ((items + gr - 1) / gr) * (uint64_t)((nt + s - 1) / s);
+    const uint64_t cost = (uint64_t)((qt * s + gr - 1) / gr) * ((nt + s - 1) / s);
     if (cost < best_cost || (cost == best_cost && s < best)) {
       best_cost = cost;
       best = s;
     }
+    if (s == cap) break;   // (larger r give the same S)
   }
   sp.S = best;
   return sp;
