@@ -42,8 +42,9 @@ def traffic_file(workload: str) -> str:
     return os.path.join(ROOT, "profiles", f"score_step_{workload}_traffic.json")
 
 
-KERNEL_SOURCES = ["paper_2607_22578_amd/csrc/score_mfma.hip", "paper_2607_22578_amd/csrc/score.hip",
-                  "paper_2607_22578_amd/csrc/common.h"]
+KERNEL_SOURCES = ["paper_2607_22578_amd/csrc/score_mfma.hip",
+                  "paper_2607_22578_amd/csrc/score_f32.hip", "paper_2607_22578_amd/csrc/score.hip",
+                  "paper_2607_22578_amd/csrc/score_lists.h", "paper_2607_22578_amd/csrc/common.h"]
 # The score step (hs_score_partial) is four launches on one stream: the query
 # tiling, the seed pass, the seed selection (which also restarts the shared
 # thresholds) and the main pass.  Its HIP-event duration is the sum of those
@@ -51,7 +52,8 @@ KERNEL_SOURCES = ["paper_2607_22578_amd/csrc/score_mfma.hip", "paper_2607_22578_
 EV_EVERY = 4
 SCORE_STEP = ("score step = tile_queries_kernel + score_mfma_dma (seed pass) + mfma_seed_kernel "
               "+ score_mfma_dma (main pass)")
-SCORE_STEP_VALU = "score step = score_partial_valu (fp32, vector units)"
+SCORE_STEP_F32 = ("score step = score_f32_mfma (fp32 matrix cores; with its seed pass where "
+                  "slices have several tiles)")
 
 
 DEDUP_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dedup_gather_dedup256k_traffic.json")
@@ -384,7 +386,7 @@ def main():
     t_mfma = alg_flops / (PEAK_MFMA["bf16"] * 1e12)
     t_hbm = alg_bytes / (PEAK_HBM_GBS * 1e9)
     t_alu = alg_flops / (PEAK_FP32_VECTOR * 1e12)
-    if f32 and t_alu >= t_hbm:   # fp32 inputs run on the vector units
+    if f32 and t_alu >= t_hbm:   # (the fp32 matrix peak is the vector peak)
         roof = {"bound": "alu", "achieved": round(tflops, 3), "peak": PEAK_FP32_VECTOR,
                 "unit": "TFLOP/s", "frac": round(tflops / PEAK_FP32_VECTOR, 4)}
     elif f32:
@@ -397,7 +399,7 @@ def main():
         roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS,
                 "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4)}
     roof["traffic"] = None
-    roof["kernel"] = SCORE_STEP_VALU if f32 else SCORE_STEP
+    roof["kernel"] = SCORE_STEP_F32 if f32 else SCORE_STEP
     roof["kernel_ms"] = round(kern_ms, 4)
     roof["kernel_ms_p10_p50_p90"] = [round(float(np.percentile(kern_samples, p)), 4)
                                      for p in (10, 50, 90)]

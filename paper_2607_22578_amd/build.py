@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libhsmerge.so")
 BUILD = os.path.join(HERE, "_build")
 SOURCES = ["api.cpp", "cache.hip", "dedup.hip", "gather.hip", "noalloc.hip", "priority.hip",
-           "score.hip", "score_mfma.hip", "signature.hip"]
+           "score.hip", "score_f32.hip", "score_mfma.hip", "signature.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Wno-unused-function", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

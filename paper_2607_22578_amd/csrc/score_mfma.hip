@@ -62,7 +62,7 @@
 #include <mutex>
 #include <type_traits>
 
-#include "common.h"
+#include "score_lists.h"
 
 namespace hs {
 
@@ -75,9 +75,7 @@ constexpr int kMT = kMW * 64;            // threads
 constexpr int kMRB = 3;                  // 32-row blocks per wave
 constexpr int kMQB = 4;                  // 32-query blocks per tile
 constexpr int kMNC = kMW * 32 * kMRB;    // 384 corpus rows per tile
-constexpr int kMMQ = 32 * kMQB;          // 128 queries per tile
 constexpr int kMKC = 64;                 // K per ring stage (four 16-deep MFMA steps)
-constexpr int kMQcap = 8;                // queue slots per query and round
 constexpr int kMVals = 16 * kMRB;        // scores per lane and query per tile
 constexpr int kMLanesQ = kMW * 2;        // lanes holding one query in a tile
 
@@ -107,12 +105,9 @@ constexpr int kSeedSlices = 128;
 __host__ __device__ __forceinline__ int64_t seed_stride(int64_t S) {
   return S > kSeedSlices ? (S + kSeedSlices - 1) / kSeedSlices : 1;
 }
-constexpr int kMSplitMaxSK = 8192;       // bound on S*k (merge list length)
 constexpr int kMRowsW = 32 * kMRB;       // rows per wave in a tile
 constexpr int kMSS = kMNC + 128 - kMRowsW;  // row-scale slot stride (floats): the
                                          // last wave's two 64-row copies overhang
-constexpr int kMLdsMax = 160 * 1024;     // LDS per workgroup on gfx950
-constexpr int kMGridMax = 512;           // persistent grid never exceeds this
 constexpr int kMGts = kMMQ + 32;         // shared-threshold slot stride (entries): the
                                          // last wave's 64-entry copy overhangs
 
@@ -133,18 +128,6 @@ struct Geo {
   static constexpr int apieces = arow / 16;       // 16-byte pieces of a corpus row stage
   static constexpr int bpieces = brow / 16;
 };
-
-// Slot of 16-byte piece p in a row of P pieces.  gfx950's LDS serves a
-// ds_read_b128 16 lanes at a time over 64 banks (256 bytes); the fragment
-// reads have 16 consecutive rows read the same piece, so the 16 / P rows that
-// share a 256-byte window must get distinct slots, for every p: the slot is p
-// XOR the row's window number (mod P).  Only row mod 16 matters.
-template <int P>
-__device__ __forceinline__ int swz_slot(int p, int row) {
-  return p ^ ((row / (16 / P)) & (P - 1));
-}
-
-constexpr int kMTail = 16;   // list entries kept in LDS when the lists are global
 
 // Order statistics a finished item publishes per query: level l holds the
 // ordered score of the ceil(k / r)-th best key of the slice's final list,
@@ -194,92 +177,6 @@ __device__ __forceinline__ void cvt8_fp8_bf16(uint32_t lo, uint32_t hi, bf16x8m 
                        __builtin_bit_cast(uint32_t, c), __builtin_bit_cast(uint32_t, e));
   out = __builtin_bit_cast(bf16x8m, v);
 }
-
-// Barrier for LDS data: this wave's LDS operations complete, then s_barrier.
-// No memory fence, so copies into the ring stay in flight across it.
-__device__ __forceinline__ void bar_lds() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// Wait until at most n of this wave's vector-memory operations are pending
-// (they complete in issue order).  n is one of the few values a ring depth
-// can produce.
-__device__ __forceinline__ void wait_vm(int n) {
-  __builtin_amdgcn_sched_barrier(0);
-  switch (n) {
-#define HS_VM_CASE(x) \
-  case x: asm volatile("s_waitcnt vmcnt(" #x ")" ::: "memory"); break;
-    HS_VM_CASE(1) HS_VM_CASE(2) HS_VM_CASE(3) HS_VM_CASE(4) HS_VM_CASE(5) HS_VM_CASE(6)
-    HS_VM_CASE(7) HS_VM_CASE(8) HS_VM_CASE(9) HS_VM_CASE(10) HS_VM_CASE(11) HS_VM_CASE(12)
-    HS_VM_CASE(13) HS_VM_CASE(14) HS_VM_CASE(15) HS_VM_CASE(16) HS_VM_CASE(17) HS_VM_CASE(18)
-    HS_VM_CASE(19) HS_VM_CASE(20) HS_VM_CASE(21) HS_VM_CASE(22) HS_VM_CASE(23) HS_VM_CASE(24)
-    HS_VM_CASE(25) HS_VM_CASE(26) HS_VM_CASE(27) HS_VM_CASE(28) HS_VM_CASE(29) HS_VM_CASE(30)
-    HS_VM_CASE(31) HS_VM_CASE(32)
-#undef HS_VM_CASE
-    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-  }
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// Buffer descriptor (raw, stride 0) over [base, base + bytes): loads at
-// offsets past `bytes` return zeros and touch no memory.
-typedef int i32x4m __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ i32x4m make_rsrc(const void *base, uint32_t bytes) {
-  // (the operands are wave-uniform; readfirstlane puts them in SGPRs)
-  const uint64_t p = (uint64_t)base;
-  i32x4m r;
-  r.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
-  r.y = __builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xFFFFu));
-  r.z = __builtin_amdgcn_readfirstlane((int)bytes);
-  r.w = 0x00020000;
-  return r;
-}
-
-// Asynchronous copies global -> LDS (buffer_load ... lds): lane l writes its
-// 16 (or 4) bytes at lds + 16 l (or 4 l).  They are issued from inline asm
-// on purpose: the compiler cannot tell which LDS bytes such a copy writes,
-// so for the builtin form it drains every copy in flight before any later
-// LDS read, which would defeat the ring.  The kernel orders the copies
-// itself (wait_vm, then a barrier).  M0 holds the LDS base; the compiler
-// reserves M0 and sets it before each of its own uses, so overwriting it
-// here is harmless.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(i32x4m rsrc, const void *lds, uint32_t voff) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(l), "v"(voff), "s"(rsrc) : "memory", "m0");
-}
-__device__ __forceinline__ void dma4(i32x4m rsrc, const void *lds, uint32_t voff) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-               :: "s"(l), "v"(voff), "s"(rsrc) : "memory", "m0");
-}
-__device__ __forceinline__ void dma16s(i32x4m rsrc, uint32_t lds, uint32_t voff) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(lds);
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(l), "v"(voff), "s"(rsrc) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-struct MfmaArgs {
-  const void *q;
-  const void *corpus;
-  const float *scale;
-  int64_t N, d;
-  int k;
-  int64_t n_unique;
-  const int64_t *n_unique_dev;
-  int64_t cap;
-  int grid;
-  int tiled;        // corpus in the tiled layout (tile_corpus_kernel), else row-major
-  uint64_t *part;
-  uint32_t *gthr;   // [cap] per-query shared thresholds (ordered score, 0 = none)
-  uint32_t *lmax;   // [n_u][S][T][8] lane maxima of the seed pass (ordered scores)
-  uint32_t *lvl;    // [n_u][kLvl][S] order statistics of finished items (ordered scores)
-};
 
 // Fragments of one half stage (two 16-deep steps).  The K order inside a
 // stage is permuted identically for both operands: step t in 0..3 and lane
@@ -391,22 +288,6 @@ __device__ __forceinline__ void mfma_step_il(f32x16m (&acc)[kMRB][NQB], const Fr
   }
 }
 
-struct MLds {
-  unsigned char *ring;
-  float *sscale;     // [nsc][kMSS] row scales of the tiles in flight (fp8)
-  uint32_t *gtl;     // [ngt][kMGts] shared thresholds of the tiles in flight
-  uint64_t *queue;   // [MQ][kMQcap] keys queued this round
-  int32_t *qcount;   // [MQ] keys queued (may exceed kMQcap: overflow)
-  float *thr0;       // [MQ] warm-up threshold of the item
-  float *thr;        // [MQ] current threshold
-  uint32_t *pub;     // [MQ] last threshold published to the shared array
-  uint64_t *lmin;    // [MQ] last key of the sorted list when full, else its fill count
-  float *warm;       // [kMW][MQ] per-wave minima of group maxima (aliases queue)
-  int32_t *flags;    // [1] overflow epoch, [2] merge-due epoch
-  uint64_t *lists;   // [MQ][k] or nullptr (lists in the global partial buffer)
-  uint64_t *tail;    // [MQ][kMTail] last entries of the global lists, or nullptr
-};
-
 template <bool FP8, bool LDS_LISTS>
 __device__ __forceinline__ MLds carve_mlds(unsigned char *p, int k) {
   using G = Geo<FP8>;
@@ -427,25 +308,6 @@ __device__ __forceinline__ MLds carve_mlds(unsigned char *p, int k) {
   L.tail = LDS_LISTS ? nullptr : reinterpret_cast<uint64_t *>(p);
   (void)k;
   return L;
-}
-
-struct MItem {
-  int qbase, qvalid, s;
-  int64_t S;
-  int T;   // tiles per slice of the seed pass sample
-};
-
-// Publish query t's threshold (a lower bound of its k-th best score over its
-// slice, hence over the whole corpus) to the per-query shared array: every
-// slice of the query filters with the largest bound any slice has reached.
-__device__ __forceinline__ void publish_thr(const MLds &L, const MfmaArgs &a, const MItem &it,
-                                            int t, float th) {
-  if (!(th > -__builtin_inff())) return;
-  const uint32_t o = ord_score(th);
-  if (o > L.pub[t]) {
-    L.pub[t] = o;
-    atomicMax(a.gthr + it.qbase + t, o);
-  }
 }
 
 // Keep t (descending) the R largest of the values offered so far.
@@ -491,84 +353,6 @@ __device__ __forceinline__ uint32_t level_bound(const uint32_t *lv, int S) {
   b = t3[7] > b ? t3[7] : b;
   b = t4[15] > b ? t4[15] : b;
   return b;
-}
-
-// Merge the queued keys of query t into its k-list (one thread per query).
-// The list is kept sorted in descending key order (empty slots are key 0 at
-// the end), so its minimum is always the last entry and an insertion only
-// shifts the entries it passes: near the threshold, where nearly every
-// entrant lands, that is one or two steps.  A list in the global partial
-// buffer keeps its last kMTail entries in LDS while the item runs (its head,
-// positions [0, k - kMTail), stays in global memory): an insertion touches
-// global memory only when its key climbs above that window.
-template <bool LDS_LISTS>
-__device__ __forceinline__ void merge_queue(const MLds &L, const MfmaArgs &a, const MItem &it,
-                                            int t) {
-  const int cnt = L.qcount[t];
-  if (cnt <= 0) return;
-  const int n = cnt < kMQcap ? cnt : kMQcap;
-  const int k = a.k;
-  const int hb = LDS_LISTS ? k : k - kMTail;   // first position held in the LDS tail
-  uint64_t *l = LDS_LISTS ? L.lists + t * k
-                          : a.part + ((int64_t)(it.qbase + t) * it.S + it.s) * k;
-  uint64_t *tail = LDS_LISTS ? nullptr : L.tail + t * kMTail;
-  auto get = [&](int i) -> uint64_t { return (!LDS_LISTS && i >= hb) ? tail[i - hb] : l[i]; };
-  auto set = [&](int i, uint64_t v) {
-    if (!LDS_LISTS && i >= hb)
-      tail[i - hb] = v;
-    else
-      l[i] = v;
-  };
-  // lmin holds the list's last key once the list is full, else its fill
-  // count (below 2^32, hence below every key: a real key's ordered score is
-  // nonzero), so that an entrant of a list that is not full starts at the
-  // first empty slot instead of climbing over the empty ones
-  uint64_t mn = L.lmin[t];
-  int fill = (mn >> 32) ? k : (int)mn;
-  for (int e = 0; e < n; ++e) {
-    const uint64_t key = L.queue[t * kMQcap + e];
-    if (key > mn) {
-      int i = fill < k ? fill : k - 1;   // the key's slot if no entry above is smaller
-      if constexpr (LDS_LISTS) {
-        while (i > 0) {
-          const uint64_t prev = get(i - 1);
-          if (prev > key) break;
-          set(i, prev);
-          --i;
-        }
-      } else {
-        // climb in windows of 8 entries read together (independent global
-        // loads): the window's entries above the key stay, the others move
-        // down by one
-        while (i > 0) {
-          const int lo = i > 8 ? i - 8 : 0;
-          uint64_t b[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) b[u] = lo + u < i ? get(lo + u) : 0ull;   // (0: not above)
-          int above = 0;
-#pragma unroll
-          for (int u = 0; u < 8; ++u) above += b[u] > key ? 1 : 0;
-#pragma unroll
-          for (int u = 7; u >= 0; --u)
-            if (u >= above && lo + u < i) set(lo + u + 1, b[u]);
-          if (above > 0 || lo == 0) {
-            i = lo + above;
-            break;
-          }
-          i = lo;
-        }
-      }
-      set(i, key);
-      if (fill < k) ++fill;
-      mn = fill == k ? get(k - 1) : (uint64_t)fill;
-    }
-  }
-  L.lmin[t] = mn;
-  const float tl = (mn >> 32) ? unord_score((uint32_t)(mn >> 32)) : -__builtin_inff();
-  const float t0v = L.thr0[t];
-  L.thr[t] = tl > t0v ? tl : t0v;
-  publish_thr(L, a, it, t, L.thr[t]);
-  L.qcount[t] = 0;
 }
 
 // Keep the accumulators in AGPRs and make the compiler forget any VGPR copy
@@ -1244,7 +1028,7 @@ __global__ __launch_bounds__(kMT, 1) void score_mfma_dma(MfmaArgs a) {
 
 // ---------------------------------------------------------------- host side
 
-int persistent_grid(bool mfma);
+int persistent_grid();
 
 // Score workspace of the matrix-core path: [shared thresholds, cap x u32]
 // (rounded to 256 bytes) followed by the partial lists.
@@ -1346,6 +1130,7 @@ static hipError_t launch_mfma(K kern, int grid, int lds, const MfmaArgs &a, hipS
 // the largest digit whose count of values at or above it reaches the rank
 // still sought.
 constexpr int kSeedThreads = 256;
+template <bool F32>
 __global__ __launch_bounds__(kSeedThreads) void mfma_seed_kernel(
     const uint32_t *__restrict__ lmax, int64_t n_unique, const int64_t *__restrict__ nu_dev,
     int64_t cap, int64_t N, int k, int64_t smax, int grid, uint32_t *__restrict__ gthr,
@@ -1354,14 +1139,21 @@ __global__ __launch_bounds__(kSeedThreads) void mfma_seed_kernel(
   __shared__ uint32_t hist[256];
   __shared__ uint32_t sel[2];   // chosen digit, values above it
   const int64_t nu = read_nu(n_unique, nu_dev, cap);
-  const Split sp = make_split(nu, N, kMMQ, kMNC, grid, smax);
-  const int64_t per = sp.S * kMLanesQ * seed_tiles(k, sp.ntiles, sp.S);
+  const Split sp = make_split(nu, N, kMMQ, F32 ? kFNC : kMNC, grid, smax);
+  int64_t per;
+  if (F32) {
+    const int64_t stride = f32_seed_stride(sp.S);
+    per = f32_seeded(sp) ? (sp.S + stride - 1) / stride * kFGroups : 0;
+  } else {
+    per = sp.S * kMLanesQ * seed_tiles(k, sp.ntiles, sp.S);
+  }
   const int n = (int)(per < kSeedMax ? per : kSeedMax);
   const int tid = threadIdx.x;
   // no item of this call has finished yet: no published order statistics
-  for (int64_t e = (int64_t)blockIdx.x * kSeedThreads + tid; e < nu * kLvl * sp.S;
-       e += (int64_t)gridDim.x * kSeedThreads)
-    lvl[e] = 0u;
+  if (!F32)
+    for (int64_t e = (int64_t)blockIdx.x * kSeedThreads + tid; e < nu * kLvl * sp.S;
+         e += (int64_t)gridDim.x * kSeedThreads)
+      lvl[e] = 0u;
   if (n < k) {   // fewer lane maxima than k: no seed
     for (int64_t q = (int64_t)blockIdx.x * kSeedThreads + tid; q < nu;
          q += (int64_t)gridDim.x * kSeedThreads)
@@ -1421,6 +1213,16 @@ __global__ __launch_bounds__(kSeedThreads) void mfma_seed_kernel(
   }
 }
 
+hipError_t launch_seed_select(const MfmaArgs &a, int64_t smax, bool f32, hipStream_t st) {
+  const int64_t want = a.n_unique >= 0 ? a.n_unique : a.cap;
+  const int64_t blocks = want < 4 * (int64_t)a.grid ? want : 4 * (int64_t)a.grid;
+  if (blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(f32 ? mfma_seed_kernel<true> : mfma_seed_kernel<false>,
+                     dim3((unsigned)blocks), dim3(kSeedThreads), 0, st, a.lmax, a.n_unique,
+                     a.n_unique_dev, a.cap, a.N, a.k, smax, a.grid, a.gthr, a.lvl);
+  return hipGetLastError();
+}
+
 // Tiled corpus layout.  Tile t (corpus rows [384 t, 384 t + 384)) and stage s
 // (columns [64 s, 64 s + 64)) form one block of Geo::abytes bytes at
 // (t * nch + s) * Geo::abytes, nch = ceil(d / 64): the stage exactly as the
@@ -1455,14 +1257,15 @@ __global__ __launch_bounds__(256) void tile_corpus_kernel(const unsigned char *_
 }
 
 // The distinct queries in the same order, per query tile: tile u (queries
-// [128 u, 128 u + 128)) and stage s form the 16 KiB block u * nch + s, row r
-// of the tile at r * 128 bytes with its pieces in the swizzled slots; queries
-// past n_u and columns past d are zeros.  Written into the score workspace at
-// the start of every score call (n_u * d * 2 bytes read, the tiles' bytes
-// written), so that the score kernel's query copies read consecutive KiB too.
+// [128 u, 128 u + 128)) and stage s (128 bytes of each row: 64 bf16 or 32 fp32
+// columns) form the 16 KiB block u * nch + s, row r of the tile at r * 128
+// bytes with its pieces in the swizzled slots; queries past n_u and columns
+// past d are zeros.  Written into the score workspace at the start of every
+// score call (the queries' bytes read, the tiles' bytes written), so that the
+// score kernels' query copies read consecutive KiB too.
 __global__ __launch_bounds__(256) void tile_queries_kernel(
     const unsigned char *__restrict__ q, int64_t n_unique, const int64_t *__restrict__ nu_dev,
-    int64_t cap, int64_t d, int nch, uint4 *__restrict__ dst) {
+    int64_t cap, int64_t row_bytes, int nch, uint4 *__restrict__ dst) {
   constexpr int PB = Geo<false>::bpieces;
   constexpr int per_stage = Geo<false>::bbytes / 16;
   const int64_t nu = read_nu(n_unique, nu_dev, cap);
@@ -1476,16 +1279,30 @@ __global__ __launch_bounds__(256) void tile_queries_kernel(
     const int r = in / PB;
     const int piece = swz_slot<PB>(in % PB, r);
     const int64_t row = u * kMMQ + r;
-    const int64_t col = (int64_t)s * kMKC + piece * 8;
+    const int64_t col = (int64_t)s * Geo<false>::brow + piece * 16;
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (row < nu && col < d) v = *reinterpret_cast<const uint4 *>(q + (row * d + col) * 2);
+    if (row < nu && col < row_bytes)
+      v = *reinterpret_cast<const uint4 *>(q + row * row_bytes + col);
     dst[p] = v;
   }
 }
 
-// Bytes of the tiled queries for up to cap distinct queries.
-size_t mfma_qtile_bytes(int64_t cap, int64_t d) {
-  return (size_t)((cap + kMMQ - 1) / kMMQ) * (size_t)((d + kMKC - 1) / kMKC) * Geo<false>::bbytes;
+// Bytes of the tiled queries for up to cap distinct queries of row_bytes each.
+size_t qtile_bytes(int64_t cap, int64_t row_bytes) {
+  return (size_t)((cap + kMMQ - 1) / kMMQ) *
+         (size_t)((row_bytes + Geo<false>::brow - 1) / Geo<false>::brow) * Geo<false>::bbytes;
+}
+
+hipError_t launch_tile_queries(const void *q, int64_t n_unique, const int64_t *nu_dev, int64_t cap,
+                               int64_t row_bytes, void *dst, hipStream_t st) {
+  if (cap <= 0) return hipSuccess;
+  const int64_t want = (int64_t)(qtile_bytes(cap, row_bytes) / 16 + 255) / 256;
+  const unsigned blocks = (unsigned)(want < 2048 ? want : 2048);
+  const int nch = (int)((row_bytes + Geo<false>::brow - 1) / Geo<false>::brow);
+  hipLaunchKernelGGL(tile_queries_kernel, dim3(blocks), dim3(256), 0, st,
+                     (const unsigned char *)q, n_unique, nu_dev, cap, row_bytes, nch,
+                     (uint4 *)dst);
+  return hipGetLastError();
 }
 
 // Offset of the tiled queries in the score workspace (after the partial lists).
@@ -1524,15 +1341,8 @@ hipError_t launch_score_mfma(const void *q, const void *corpus, const float *sca
                                mfma_lmax_bytes(cap, N, k, kMGridMax));
   void *part = (unsigned char *)ws + mfma_part_offset(cap, N, k, kMGridMax);
   void *qt = (unsigned char *)ws + mfma_qtile_offset(cap, N, k, kMGridMax);
-  if (cap > 0) {
-    const int nch = (int)((d + kMKC - 1) / kMKC);
-    const int64_t want = (int64_t)(mfma_qtile_bytes(cap, d) / 16 + 255) / 256;
-    const unsigned blocks = (unsigned)(want < 2048 ? want : 2048);
-    hipLaunchKernelGGL(tile_queries_kernel, dim3(blocks), dim3(256), 0, st,
-                       (const unsigned char *)q, n_unique, nu_dev, cap, d, nch, (uint4 *)qt);
-    hipError_t e0 = hipGetLastError();
-    if (e0 != hipSuccess) return e0;
-  }
+  hipError_t e = launch_tile_queries(q, n_unique, nu_dev, cap, d * 2, qt, st);
+  if (e != hipSuccess) return e;
   MfmaArgs a;
   a.q = qt;
   a.corpus = corpus;
@@ -1547,7 +1357,7 @@ hipError_t launch_score_mfma(const void *q, const void *corpus, const float *sca
   a.gthr = gthr;
   a.lmax = lmax;
   a.lvl = lvl;
-  a.grid = persistent_grid(true);
+  a.grid = persistent_grid();
   a.tiled = tiled ? 1 : 0;
   // k-lists in LDS when they fit beside the ring
   const bool ll = mfma_lds_bytes(fp8, true, k) <= kMLdsMax;
@@ -1567,20 +1377,11 @@ hipError_t launch_score_mfma(const void *q, const void *corpus, const float *sca
   // a sample of tiles spread over it)
   // seeds the shared thresholds.  The main pass then scores every tile with
   // lists that stay nearly untouched from the first tile on.
-  hipError_t e = run(true);
+  e = run(true);
   if (e != hipSuccess) return e;
-  if (cap > 0) {
-    int64_t smax = kMSplitMaxSK / k;
-    if (smax < 1) smax = 1;
-    const int64_t want = n_unique >= 0 ? n_unique : cap;
-    const int64_t blocks = want < 4 * (int64_t)a.grid ? want : 4 * (int64_t)a.grid;
-    if (blocks > 0) {
-      hipLaunchKernelGGL(mfma_seed_kernel, dim3((unsigned)blocks), dim3(kSeedThreads), 0, st,
-                         a.lmax, n_unique, nu_dev, cap, N, k, smax, a.grid, gthr, a.lvl);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-  }
+  int64_t smax = kMSplitMaxSK / k;
+  e = launch_seed_select(a, smax < 1 ? 1 : smax, false, st);
+  if (e != hipSuccess) return e;
   return run(false);
 }
 

@@ -1,0 +1,81 @@
+"""fp32 score path at the edges of its variants: query counts around the
+32-query blocks and the 128-query tile (one block splits the columns over four
+waves, two over two), corpora around its 64-row tiles, slices of one tile (ranked),
+of a few tiles, and of many (seeded), lists of up to 16 keys (in LDS) and more."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_harness import check_dedup, check_unique_topk, device, note, run_merge, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(n, d, stream):
+    return synth.gaussian_rows(77, stream, n, d, "f32")[0]
+
+
+# 70,001 rows of 64-row tiles are 1,094 tiles: more than four in each of the 256
+# slices of one query tile, so the seed pass runs; 2,501 rows are 40 one-tile
+# slices; 300 queries over 20,011 rows make slices of a few tiles, unseeded.
+@pytest.mark.parametrize("nu,n,d,k", [
+    (1, 1, 4, 1), (1, 63, 28, 16), (31, 64, 32, 17), (32, 65, 36, 10), (33, 2_501, 100, 16),
+    (64, 2_501, 96, 17), (65, 2_501, 64, 10), (128, 2_501, 68, 40), (129, 2_501, 64, 10),
+    (300, 20_011, 32, 10), (20, 70_001, 36, 10), (40, 70_001, 36, 17), (120, 70_001, 36, 1),
+    (130, 70_001, 36, 100),
+])
+def test_f32_variant_edges(nu, n, d, k):
+    note(f"fp32 n_u={nu} N={n} d={d} k={k}")
+    keys = np.random.default_rng(nu).permutation(nu).astype(np.int64)
+    q, c = _rows(nu, d, 201), _rows(n, d, 202)
+    m = run_merge(keys, q, c, k)
+    check_unique_topk(m, check_dedup(m, keys), q, c, k)
+
+
+@pytest.mark.parametrize("n", [2_501, 70_001])
+def test_f32_scores_do_not_depend_on_the_batch(n):
+    # the sum of a score has one order whatever the batch: the first b queries
+    # alone (through each variant) give the rows they have in the batch of 130
+    import paper_2607_22578_amd as hs
+    d, k, nu = 100, 12, 130
+    q, c = _rows(nu, d, 203), _rows(n, d, 204)
+    c[n // 2] = c[7]                     # equal rows: bit-identical scores, lower row first
+    q[3] = c[7]
+    dev = device()
+    m = hs.MergedRetrieval(nu, d, n, k, hs.HS_F32, hs.HS_F32, device=dev)
+    qd, cd = to_dev(q), to_dev(c)
+    m.q_unique[:nu].copy_(qd)
+
+    def score(b):
+        hs.hs_score_topk(m.plan, m.q_unique, b, None, cd, None, m.topk_score, m.topk_index, m.ws)
+        torch.cuda.synchronize()
+        return m.topk_score[:b].cpu().numpy().copy(), m.topk_index[:b].cpu().numpy().copy()
+
+    all_s, all_i = score(nu)
+    assert list(all_i[3][:2]) == [7, n // 2]
+    assert all_s[3][0].view(np.uint32) == all_s[3][1].view(np.uint32)
+    for b in (1, 32, 33, 64, 65, 128, 129):
+        s, i = score(b)
+        np.testing.assert_array_equal(i, all_i[:b])
+        np.testing.assert_array_equal(s.view(np.uint32), all_s[:b].view(np.uint32))
+
+
+@pytest.mark.parametrize("n,k", [(40, 10), (2_501, 20)])
+def test_f32_infinite_and_nan_rows(n, k):
+    # a NaN score is never ranked; infinities are, in their places
+    d, nu = 32, 3
+    keys = np.arange(nu, dtype=np.int64)
+    q, c = np.abs(_rows(nu, d, 205)) + 0.1, _rows(n, d, 206)
+    c[5] = np.nan
+    c[9] = np.inf
+    c[11] = -np.inf
+    c[13, 0], c[13, 1] = np.inf, -np.inf  # NaN sum
+    m = run_merge(keys, q, c, k)
+    s, i = m.topk_score[:nu].cpu().numpy(), m.topk_index[:nu].cpu().numpy()
+    finite = np.setdiff1d(np.arange(n), [5, 9, 11, 13])
+    for u in range(nu):
+        assert i[u][0] == 9 and np.isposinf(s[u][0])
+        exact = c[finite].astype(np.float64) @ q[u].astype(np.float64)
+        order = finite[np.argsort(-exact, kind="stable")][:k - 1]
+        np.testing.assert_array_equal(i[u][1:], order)
