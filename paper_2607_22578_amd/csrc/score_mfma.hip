@@ -261,7 +261,9 @@ __device__ __forceinline__ void mfma_step(f32x16m (&acc)[kMRB][NQB], const Frag<
           av[rb], __builtin_bit_cast(bf16x8m, f.b[s][qb]), ZERO ? zero : acc[rb][qb], 0, 0, 0);
 }
 
-template <bool FP8, bool ZERO, int NOPS, int NQB, typename Op>
+// The same with op(i) issued after the i-th matrix instruction, in its shadow
+// (a scheduling barrier after each keeps the order).
+template <bool FP8, bool ZERO, int NQB, typename Op>
 __device__ __forceinline__ void mfma_step_il(f32x16m (&acc)[kMRB][NQB], const Frag<FP8, NQB> &f,
                                              int s, Op &&op) {
   bf16x8m av[kMRB];
@@ -276,14 +278,12 @@ __device__ __forceinline__ void mfma_step_il(f32x16m (&acc)[kMRB][NQB], const Fr
     }
   }
   const f32x16m zero = {};
-  constexpr int NM = kMRB * NQB;
 #pragma unroll
-  for (int i = 0; i < NM; ++i) {
+  for (int i = 0; i < kMRB * NQB; ++i) {
     const int rb = i / NQB, qb = i % NQB;
     acc[rb][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
         av[rb], __builtin_bit_cast(bf16x8m, f.b[s][qb]), ZERO ? zero : acc[rb][qb], 0, 0, 0);
-#pragma unroll
-    for (int k = i * NOPS / NM; k < (i + 1) * NOPS / NM; ++k) op(k);
+    op(i);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -851,16 +851,6 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
       for (int j = 0; j < G::bdma; ++j) issue_b_j(cb, j);
       extras_advance();
     };
-    // Vector-memory operations issued after the query part of chunk y, up
-    // to the corpus part of chunk z (only z's corpus part is issued yet).
-    // Tile-first extras are not counted: waiting for fewer outstanding
-    // operations only waits longer.
-    auto younger_ops = [&](int y, int z) __attribute__((always_inline)) {
-      int n = 0;
-      for (int x = y + 1; x <= z && x < T; ++x) n += x < z ? G::ldma : G::adma;
-      return n;
-    };
-
 #pragma unroll
     for (int j = 0; j < G::ns; ++j) {
       issue_a();
@@ -888,41 +878,71 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
     // (Moving the whole copy earlier costs a second barrier per stage, which
     // was slower: the loop is bound by the matrix cores sharing the CU with
     // the LDS reads more than by copy latency.)
-    auto stage = [&](auto first_c, bool rd) __attribute__((always_inline)) {
-      constexpr bool FIRST = decltype(first_c)::value;
-      constexpr int NR = Frag<FP8, NQB>::nreads;
+    // There is one wave per SIMD, so whatever stands between two matrix
+    // instructions without being in the shadow of one is lost: the reads go two
+    // or three to an instruction and so have landed when the next half needs
+    // them, and the bookkeeping of the copies (stream position, descriptors,
+    // offsets) is done behind matrix instructions of the steps that have
+    // little else to issue, ahead of the step that uses it.
+    constexpr int NR = Frag<FP8, NQB>::nreads, NM = kMRB * NQB;
+    constexpr int RPM = (NR + NM - 1) / NM < 2 ? 2 : (NR + NM - 1) / NM;   // reads per MFMA
+    constexpr int CPA = (G::adma + NM - 1) / NM, CPB = (G::bdma + NM - 1) / NM;
+    auto stage = [&](auto first_c, auto rd_c) __attribute__((always_inline)) {
+      constexpr bool FIRST = decltype(first_c)::value, RD = decltype(rd_c)::value;
       const unsigned char *cur = L.ring + r_slot * G::stage;
       const int ln1 = opaque(lane);
-      mfma_step_il<FP8, FIRST, NR>(acc, f0, 0, [&](int k) __attribute__((always_inline)) {
-        read_frag_piece<FP8>(f1, cur, wv, ln1 & 31, ln1 >> 5, 1, k);
+      CopyA ca;
+      mfma_step_il<FP8, FIRST>(acc, f0, 0, [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = RPM * i; k < RPM * (i + 1); ++k)
+          if (k < NR) read_frag_piece<FP8>(f1, cur, wv, ln1 & 31, ln1 >> 5, 1, k);
+        if (i == (NM > 8 ? 8 : NM - 1)) {
+          // the previous stage's chunk is done with; this wave's corpus rows of
+          // stage g+ns are next
+          if (g > 0) extras_advance();
+          ca = prep_a();
+          if (i_left <= 0) ca.rs.z = 0;
+        }
       });
-      {
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        CopyA ca = prep_a();   // this wave's corpus rows of stage g+ns
-        if (i_left <= 0) ca.rs.z = 0;
-        mfma_step_il<FP8, false, G::adma>(acc, f0, 1, [&](int k) __attribute__((always_inline)) {
-          issue_a_j(ca, k);
-        });
-      }
-      mfma_step<FP8, false>(acc, f1, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_step_il<FP8, false>(acc, f0, 1, [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = CPA * i; k < CPA * (i + 1); ++k)
+          if (k < G::adma) issue_a_j(ca, k);
+      });
+      CopyB cb;
+      mfma_step_il<FP8, false>(acc, f1, 0, [&](int i) __attribute__((always_inline)) {
+        // query rows of stage g+ns, into the slot stage g used
+        if (i == (NM > 4 ? 4 : NM - 1)) cb = prep_b();
+      });
       r_slot = r_slot + 1 == G::ns ? 0 : r_slot + 1;
-      // stage g+1 landed (after the last stage: all copies landed):
-      // younger are the parts of stages g+2 .. g+ns issued so far
-      wait_vm(younger_ops(g + 1, g + G::ns));
+      // stage g+1 landed (after the last stage: all copies landed): younger
+      // are the parts of stages g+2 .. g+ns issued so far (a tile's thresholds
+      // and row scales are not counted: waiting for fewer outstanding
+      // operations only waits longer)
+      if (g + G::ns < T)
+        wait_vm((G::ns - 2) * G::ldma + G::adma);
+      else
+        wait_vm(0);
       bar_lds();
       pin_step1<FP8>(f1);
-      const CopyB cb = prep_b();   // query rows of stage g+ns into the slot stage g used
       const unsigned char *nxt = L.ring + r_slot * G::stage;
       const int ln0 = opaque(lane);
-      mfma_step_il<FP8, false, G::bdma + NR>(acc, f1, 1, [&](int k) __attribute__((always_inline)) {
-        if (k < G::bdma)
-          issue_b_j(cb, k);
-        else if (rd)
-          read_frag_piece<FP8>(f0, nxt, wv, ln0 & 31, ln0 >> 5, 0, k - G::bdma);
+      constexpr int R0 = RD ? (NR + RPM - 1) / RPM : 0;   // instructions that carry reads
+      constexpr int B0 = R0 < NM - (G::bdma + CPB - 1) / CPB ? R0
+                                                             : NM - (G::bdma + CPB - 1) / CPB;
+      mfma_step_il<FP8, false>(acc, f1, 1, [&](int i) __attribute__((always_inline)) {
+        if constexpr (RD) {
+#pragma unroll
+          for (int k = RPM * i; k < RPM * (i + 1); ++k)
+            if (k < NR) read_frag_piece<FP8>(f0, nxt, wv, ln0 & 31, ln0 >> 5, 0, k);
+        }
+#pragma unroll
+        for (int k = CPB * (i - B0); k < CPB * (i - B0 + 1); ++k)
+          if (k >= 0 && k < G::bdma) issue_b_j(cb, k);
       });
-      extras_advance();
       ++g;
     };
     // (the first stage of a tile starts the accumulators from zero; its call
@@ -930,8 +950,13 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
     // last stage of a tile leaves the next fragments in LDS: the epilogue runs
     // with only the accumulators live, and f0 is refilled after it.)
     for (int tl = 0; tl < ntl; ++tl) {
-      stage(std::true_type{}, nch > 1);
-      for (int j = 1; j < nch; ++j) stage(std::false_type{}, j + 1 < nch);
+      if (nch > 1) {
+        stage(std::true_type{}, std::true_type{});
+        for (int j = 1; j + 1 < nch; ++j) stage(std::false_type{}, std::true_type{});
+        stage(std::false_type{}, std::false_type{});
+      } else {
+        stage(std::true_type{}, std::false_type{});
+      }
       if constexpr (SEED)
         mtile_lane_maxima<FP8>(a, it, acc, (t0 + tl) * kMNC,
                                FP8 ? L.sscale + e_sc * kMSS : nullptr, tl);
