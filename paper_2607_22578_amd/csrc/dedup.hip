@@ -17,10 +17,13 @@
 //                    network and compacts in the same launch;
 //   larger R       : the key range is found on the device; keys that take at
 //                    most R values are grouped by direct addressing over the
-//                    range, others by an LSD radix sort (8-bit digits over
-//                    key - min, so only the bits that vary are sorted; stable
-//                    local ranking with wavefront ballots, then head flags, a
-//                    compaction and group sizes) in one persistent launch.
+//                    range; keys spread over a wide range (signatures) by a
+//                    hash table in the workspace, their distinct values
+//                    ordered bucket by bucket of the range; others by an LSD
+//                    radix sort (8-bit digits over key - min, so only the bits
+//                    that vary are sorted; stable local ranking with wavefront
+//                    ballots, then head flags, a compaction and group sizes)
+//                    in one persistent launch.
 #include "common.h"
 
 namespace hs {
@@ -268,26 +271,32 @@ __global__ __launch_bounds__(kSmallThreads) void dedup_hash_kernel(
 //             the scratch the later launches need at its neutral value;
 //   mark    : every workgroup reduces the min/max itself and picks the path;
 //             dense path (the keys take at most R values, max - min < R):
-//             first request and group size per key value;
+//             first request and group size per key value; hash path: the same
+//             per slot of the hash table, each new key also appended to its
+//             bucket of the key range;
 //   groups  : dense path: the present values numbered in ascending order by
 //             a single-pass scan (each value block looks back at the running
 //             totals of the blocks before it), with the per-group outputs;
-//   inverse : dense path: request -> group;
-//   radix   : sort path (returns at once on the dense path): one persistent
+//             hash path: each bucket's keys ranked, with the outputs;
+//   inverse : dense and hash path: request -> group;
+//   radix   : sort path (returns at once on the others): one persistent
 //             launch of at most kRadixGridMax workgroups, all resident, that
 //             runs every LSD pass (8-bit digits of key - min, one pass per
 //             8 bits of max - min), then head flags, compaction and group
 //             sizes, with grid barriers between the phases.
-// The three dense launches return at once on the sort path.
 
 constexpr int kPrepMax = 1024;        // prep workgroups (min/max partials)
 constexpr int kRadixGridMax = 256;    // workgroups of the persistent sort
 constexpr int kBarGroups = 16;        // arrival counters of the grid barrier
 constexpr int kCtlStride = 32;        // 32-bit words between counters (128 B)
-// control words: [0] value-block ticket of the groups launch; barrier
+// control words: [0] value-block ticket of the groups launch; [kCtlFull] set
+// when the hash path has given up (a bucket is full); [kCtlWide] the first keys
+// lie R or more apart; barrier
 // arrival counter j at (1 + j) * kCtlStride; the barrier's release counter at
 // (1 + kBarGroups) * kCtlStride
 constexpr int kCtlWords = (2 + kBarGroups) * kCtlStride;
+constexpr int kCtlFull = 1, kCtlWide = 2;
+constexpr int kWideKeys = 1024;
 
 struct RadixWs {
   uint64_t *keyA, *keyB;
@@ -301,7 +310,34 @@ struct RadixWs {
   int32_t *start;          // group start positions
   uint64_t *flags;         // dense value blocks: running-total words
   uint32_t *ctl;           // kCtlWords control words
+  // hash path (hbits = 0: none); everything but gid and the buckets starts at 0
+  int hbits;               // log2 of the table's slots
+  unsigned long long *hk;  // [slots] mapped keys (0: empty); slot `slots` is
+                           // that of the key that maps to 0
+  uint32_t *hfirst;        // [slots + 1] R - first request
+  uint32_t *hcnt;          // [slots + 1] group size
+  int32_t *hgid;           // [slots + 1] group
+  uint32_t *bcnt;          // [buckets] keys per bucket
+  uint64_t *bkey;          // [buckets][kBucketCap]
+  int32_t *bslot;          // [buckets][kBucketCap]
 };
+
+// Hash path.  The sort takes 8 passes for 64-bit signatures, each with two or
+// three grid barriers: 410 us for 200,000 of them, of which the bytes are 5.
+// (200,000 signatures, 95,000 distinct: marking 52 us, groups 8 us.)  The table
+// has at least 2 R slots; with R rounded up to a power of two there
+// is a bucket of the key range per 256 requests, so that uniform keys (the
+// signatures are hash values) fill a bucket to at most 256 on average, and
+// never to kBucketCap.  Keys that do are left to the sort.  Up to 2^20
+// requests: the table and the buckets take 90 bytes per request or more.
+constexpr int kHashRMax = 1 << 20;
+constexpr int kBucketCap = 1024;
+__host__ __device__ __forceinline__ int hash_bits(int64_t R) {   // 2 R <= 2^bits < 4 R
+  int b = 13;
+  while (((int64_t)1 << b) < 2 * R) ++b;
+  return b;
+}
+__host__ __device__ __forceinline__ int bucket_bits(int hbits) { return hbits - 9; }
 
 // ------------------------------------------------ grid-wide helpers
 
@@ -413,18 +449,64 @@ __global__ __launch_bounds__(kRadixThreads) void dedup_prep_kernel(
   const int64_t nvb = ((int64_t)R + 1023) / 1024;
   for (int64_t i = gt; i < nvb; i += gs) ws.flags[i] = 0ull;
   if (blockIdx.x == 0)
-    for (int i = tid; i < kCtlWords; i += kRadixThreads) ws.ctl[i] = 0u;
+    for (int i = tid; i < kCtlWords; i += kRadixThreads)
+      if (i != kCtlWide) ws.ctl[i] = 0u;
+  // The hash path is taken only where the first 1,024 keys already lie R or
+  // more apart, which every workgroup here can tell (so the dense path, whose
+  // keys do not, pays nothing for it): each then clears its share of the table
+  // and the bucket counts.
+  if (!ws.hbits) return;
+  __shared__ int wide;
+  mn = ~0ull;
+  mx = 0ull;
+#pragma unroll
+  for (int e = 0; e < kWideKeys / kRadixThreads; ++e) {
+    const uint64_t k = map_key(keys[e * kRadixThreads + tid]);   // (R > kSmallMax)
+    mn = k < mn ? k : mn;
+    mx = k > mx ? k : mx;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
+    mn = a < mn ? a : mn;
+    mx = c > mx ? c : mx;
+  }
+  __syncthreads();   // (thread 0 has read the first reduction's words)
+  if ((tid & 63) == 0) {
+    smin[tid >> 6] = mn;
+    smax[tid >> 6] = mx;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < kRadixThreads / 64; ++w) {
+      mn = smin[w] < mn ? smin[w] : mn;
+      mx = smax[w] > mx ? smax[w] : mx;
+    }
+    wide = mx - mn >= (uint64_t)R;
+    if (blockIdx.x == 0) ws.ctl[kCtlWide] = wide ? 1u : 0u;
+  }
+  __syncthreads();
+  if (!wide) return;
+  const int64_t slots = (int64_t)1 << ws.hbits;
+  for (int64_t i = gt; i <= slots; i += gs) {
+    if (i < slots) ws.hk[i] = 0ull;
+    ws.hfirst[i] = 0u;
+    ws.hcnt[i] = 0u;
+    if (i < ((int64_t)1 << bucket_bits(ws.hbits))) ws.bcnt[i] = 0u;
+  }
 }
 
 struct Range {
   uint64_t mn;
   uint64_t npass;   // radix passes (0 on the dense path)
-  uint64_t nv;      // key values of the dense path (0: radix path)
+  uint64_t nv;      // key values of the dense path (0: others)
+  int hash;         // hash path: keys - mn >> hash_shift is the bucket
+  int hash_shift;
 };
 
 // Global min/max over the P prep partials and the path: dense when the keys
-// take at most R values (max - min < R), else radix with one pass per 8 bits
-// of max - min.  Computed by every workgroup that calls it.
+// take at most R values (max - min < R), else by hashing where prep has cleared
+// the table, else radix with one pass per 8 bits of max - min.  Computed by
+// every workgroup that calls it.
 __device__ Range range_of(int R, int P, const RadixWs &ws) {
   __shared__ uint64_t smin[kRadixThreads / 64], smax[kRadixThreads / 64];
   __shared__ Range res;
@@ -455,6 +537,9 @@ __device__ Range range_of(int R, int P, const RadixWs &ws) {
     res.mn = mn;
     res.npass = dense ? 0ull : (uint64_t)((bits + kRadixBits - 1) / kRadixBits);
     res.nv = dense ? span + 1 : 0ull;
+    res.hash = !dense && ws.hbits && ws.ctl[kCtlWide] ? 1 : 0;
+    const int bb = bucket_bits(ws.hbits);
+    res.hash_shift = bits > bb ? bits - bb : 0;
   }
   __syncthreads();
   return res;
@@ -474,20 +559,179 @@ constexpr int kDenseBlk = 1024;                        // values per value block
 constexpr int kDensePer = kDenseBlk / kRadixThreads;   // values per thread
 constexpr int kAggRound = 1024, kAggSlots = 2048;
 
+// Slot search of one key in the table: the slot that holds it, claimed if need
+// be (fresh: by this call).  There are more slots than keys.
+__device__ __forceinline__ uint32_t hash_of(uint64_t m, int bits) {
+  return (uint32_t)((m * 0x9E3779B97F4A7C15ull) >> (64 - bits));
+}
+
+// Hash path of the marking launch.  Rounds of kAggRound consecutive requests
+// are first combined per key in an LDS table; the thread that entered a key
+// there looks it up in the workspace's table (its up to four keys' first
+// probes are in flight together), adds the round's first request and count to
+// its slot and, if the key is new, appends it to its bucket.  idxB gets every
+// request's slot.  Bound by the latency of a few dependent device-scope
+// atomics per key.
+__device__ void hash_insert(int R, const Range &rg, const RadixWs &ws, unsigned char *lds) {
+  constexpr int per = kAggRound / kRadixThreads;
+  unsigned long long *lk = (unsigned long long *)lds;   // mapped key (0: empty)
+  int32_t *lfirst = (int32_t *)(lds + 8 * kAggSlots);   // first request; later the slot
+  int32_t *lcnt = lfirst + kAggSlots;
+  __shared__ int32_t zfirst, zcnt;               // the key that maps to 0
+  const int tid = threadIdx.x, hbits = ws.hbits;
+  const uint32_t hmask = (1u << hbits) - 1u;
+  constexpr int lbits = 11;
+  static_assert((1 << lbits) == kAggSlots, "LDS table");
+  for (int64_t round = blockIdx.x; round * kAggRound < R; round += gridDim.x) {
+    const int64_t base = round * kAggRound;
+    for (int j = tid; j < kAggSlots; j += kRadixThreads) {
+      lk[j] = 0ull;
+      lfirst[j] = 0x7fffffff;
+      lcnt[j] = 0;
+    }
+    if (tid == 0) {
+      zfirst = 0x7fffffff;
+      zcnt = 0;
+    }
+    __syncthreads();
+    unsigned long long m[per];
+    int ls[per];          // LDS slot of the request's key (-1: none, -2: key 0)
+    bool own[per];        // this request entered it
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      const int64_t p = base + e * kRadixThreads + tid;
+      m[e] = p < R ? ws.keyA[p] : 0ull;
+      ls[e] = p < R ? -2 : -1;
+      own[e] = false;
+    }
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      const int32_t p = (int32_t)(base + e * kRadixThreads + tid);
+      if (m[e] != 0ull) {
+        uint32_t h = hash_of(m[e], lbits);
+        for (;;) {   // at most kAggRound keys in kAggSlots slots: a slot is found
+          const unsigned long long prev = atomicCAS(&lk[h], 0ull, m[e]);
+          own[e] = prev == 0ull;
+          if (prev == 0ull || prev == m[e]) break;
+          h = (h + 1) & (kAggSlots - 1);
+        }
+        ls[e] = (int)h;
+        atomicMin(&lfirst[h], p);
+        atomicAdd(&lcnt[h], 1);
+      } else if (ls[e] == -2) {
+        atomicMin(&zfirst, p);
+        atomicAdd(&zcnt, 1);
+      }
+    }
+    __syncthreads();
+    uint32_t gs[per];
+    unsigned long long prev[per];
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      gs[e] = hash_of(m[e], hbits) & hmask;
+      prev[e] = own[e] ? atomicCAS(&ws.hk[gs[e]], 0ull, m[e]) : m[e];
+    }
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      while (prev[e] != 0ull && prev[e] != m[e]) {   // (R keys, 2 R slots or more)
+        gs[e] = (gs[e] + 1) & hmask;
+        prev[e] = atomicCAS(&ws.hk[gs[e]], 0ull, m[e]);
+      }
+    }
+    auto add = [&](uint32_t slot, int32_t first, int32_t cnt) {
+      atomicMax(&ws.hfirst[slot], (uint32_t)(R - first));
+      atomicAdd(&ws.hcnt[slot], (uint32_t)cnt);
+    };
+    auto append = [&](uint64_t key, uint32_t slot) {
+      const uint32_t b = (uint32_t)((key - rg.mn) >> rg.hash_shift);
+      const uint32_t at = atomicAdd(&ws.bcnt[b], 1u);
+      if (at < (uint32_t)kBucketCap) {
+        ws.bkey[(int64_t)b * kBucketCap + at] = key;
+        ws.bslot[(int64_t)b * kBucketCap + at] = (int32_t)slot;
+      } else {
+        __hip_atomic_store(&ws.ctl[kCtlFull], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    };
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      if (!own[e]) continue;
+      add(gs[e], lfirst[ls[e]], lcnt[ls[e]]);
+      if (prev[e] == 0ull) append(m[e], gs[e]);
+      lfirst[ls[e]] = (int32_t)gs[e];   // (only its owner reads the entry here)
+    }
+    if (tid == 0 && zcnt > 0) {
+      const uint32_t slot = 1u << hbits;
+      atomicMax(&ws.hfirst[slot], (uint32_t)(R - zfirst));
+      if (atomicAdd(&ws.hcnt[slot], (uint32_t)zcnt) == 0u) append(0ull, slot);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      const int64_t p = base + e * kRadixThreads + tid;
+      if (p < R) ws.idxB[p] = ls[e] >= 0 ? lfirst[ls[e]] : (1 << hbits);
+    }
+    __syncthreads();
+  }
+}
+
+// Hash path of the groups launch: bucket b's keys are ranked by counting the
+// smaller ones (they are distinct), and its groups follow those of the buckets
+// before it.
+__device__ void hash_groups(int R, const RadixWs &ws, int64_t *__restrict__ uk,
+                            int32_t *__restrict__ fi, int32_t *__restrict__ cnt,
+                            int64_t *__restrict__ nu_out) {
+  __shared__ uint64_t sk[kBucketCap + 8];
+  __shared__ uint32_t wsum[kRadixThreads / 64 + 1];
+  if (ws.ctl[kCtlFull]) return;
+  const int tid = threadIdx.x, B = 1 << bucket_bits(ws.hbits);
+  for (int b = blockIdx.x; b < B; b += gridDim.x) {
+    uint32_t before = 0;
+    for (int i = tid; i < b; i += kRadixThreads) before += ws.bcnt[i];
+    const int n = (int)ws.bcnt[b];   // <= kBucketCap
+    for (int i = tid; i < n; i += kRadixThreads) sk[i] = ws.bkey[(int64_t)b * kBucketCap + i];
+    const int n8 = (n + 7) & ~7;
+    for (int i = n + tid; i < n8; i += kRadixThreads) sk[i] = ~0ull;   // (never below a key)
+    uint32_t total;
+    block_inclusive_scan<kRadixThreads>(before, wsum, total);   // (and a barrier for sk)
+    for (int i = tid; i < n; i += kRadixThreads) {
+      const uint64_t m = sk[i];
+      uint32_t r = total;
+      for (int j = 0; j < n8; j += 8) {
+        uint64_t y[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) y[t] = sk[j + t];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) r += y[t] < m ? 1u : 0u;
+      }
+      const int32_t slot = ws.bslot[(int64_t)b * kBucketCap + i];
+      uk[r] = unmap_key(m);
+      fi[r] = R - (int32_t)ws.hfirst[slot];
+      if (cnt) cnt[r] = (int32_t)ws.hcnt[slot];
+      ws.hgid[slot] = (int32_t)r;
+    }
+    if (b == B - 1 && tid == 0) *nu_out = (int64_t)total + n;
+    __syncthreads();
+  }
+}
+
 // Rounds of kAggRound consecutive requests are first combined per key value
 // in an LDS table (a hot key appears many times per round), then each table
 // entry goes to the value arrays with one atomic min and one atomic add.
 // Workgroup 0 also stores the path for the later launches.
 __global__ __launch_bounds__(kRadixThreads) void dense_mark_kernel(int R, int P, RadixWs ws) {
-  __shared__ int32_t tkey[kAggSlots];
-  __shared__ int32_t tfirst[kAggSlots];
-  __shared__ int32_t tcount[kAggSlots];
+  __shared__ __attribute__((aligned(16))) unsigned char lds[16 * kAggSlots];
+  int32_t *tkey = (int32_t *)lds, *tfirst = tkey + kAggSlots, *tcount = tfirst + kAggSlots;
   const Range rg = range_of(R, P, ws);
   const int tid = threadIdx.x;
   if (blockIdx.x == 0 && tid == 0) {
     ws.range[0] = rg.mn;
     ws.range[1] = rg.npass;
     ws.range[2] = rg.nv;
+    ws.range[3] = (uint64_t)rg.hash;
+  }
+  if (rg.hash) {
+    hash_insert(R, rg, ws, lds);
+    return;
   }
   if (!rg.nv) return;
   int32_t *first = (int32_t *)ws.keyB, *count = (int32_t *)ws.keyB + R;
@@ -538,6 +782,10 @@ __global__ __launch_bounds__(kRadixThreads) void dense_groups_kernel(
     int32_t *__restrict__ cnt, int64_t *__restrict__ nu_out) {
   __shared__ uint32_t wsum[kRadixThreads / 64 + 1];
   __shared__ uint32_t s_vb, s_before;
+  if (ws.range[3]) {
+    hash_groups(R, ws, uk, fi, cnt, nu_out);
+    return;
+  }
   const uint64_t nv = ws.range[2];
   const uint64_t nvb = (nv + kDenseBlk - 1) / kDenseBlk;
   if (!nv || blockIdx.x >= nvb) return;
@@ -614,6 +862,12 @@ __global__ __launch_bounds__(kRadixThreads) void dense_groups_kernel(
 __global__ __launch_bounds__(256) void dense_inverse_kernel(int R, RadixWs ws,
                                                             int32_t *__restrict__ inv) {
   const uint64_t nv = ws.range[2];
+  if (ws.range[3]) {   // hash path
+    if (ws.ctl[kCtlFull]) return;
+    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < R; p += (int64_t)gridDim.x * 256)
+      inv[p] = ws.hgid[ws.idxB[p]];
+    return;
+  }
   if (!nv) return;
   const uint64_t mn = ws.range[0];
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < R; p += (int64_t)gridDim.x * 256)
@@ -791,7 +1045,7 @@ __device__ __forceinline__ void compact_phase(int R, uint64_t npass, int b, cons
 __global__ __launch_bounds__(kRadixThreads) void radix_sort_kernel(
     int R, int nb, RadixWs ws, int64_t *__restrict__ uk, int32_t *__restrict__ fi,
     int32_t *__restrict__ cnt, int32_t *__restrict__ inv, int64_t *__restrict__ nu_out) {
-  if (ws.range[2]) return;   // dense path
+  if (ws.range[2] || (ws.range[3] && !ws.ctl[kCtlFull])) return;   // dense or hash path
   const uint64_t mn = ws.range[0], npass = ws.range[1];
   const int G = gridDim.x, b = blockIdx.x;
   uint32_t k = 0;
@@ -868,6 +1122,12 @@ size_t dedup_workspace_bytes(int64_t R) {
   s += align_up(sizeof(int32_t) * (R + 1));
   s += align_up(sizeof(uint64_t) * nvb);
   s += align_up(sizeof(uint32_t) * kCtlWords);
+  if (R <= kHashRMax) {
+    const size_t slots = (size_t)1 << hash_bits(R);
+    const size_t buckets = (size_t)1 << bucket_bits(hash_bits(R));
+    s += align_up(8 * slots) + 3 * align_up(4 * (slots + 1)) + align_up(4 * buckets);
+    s += align_up(8 * buckets * kBucketCap) + align_up(4 * buckets * kBucketCap);
+  }
   return s;
 }
 
@@ -923,7 +1183,20 @@ hipError_t launch_dedup(const int64_t *keys, int64_t R, int64_t *uk, int32_t *fi
   w.bheads = (uint32_t *)p; p += align_up(sizeof(uint32_t) * nb);
   w.start = (int32_t *)p; p += align_up(sizeof(int32_t) * (R + 1));
   w.flags = (uint64_t *)p; p += align_up(sizeof(uint64_t) * nvb);
-  w.ctl = (uint32_t *)p;
+  w.ctl = (uint32_t *)p; p += align_up(sizeof(uint32_t) * kCtlWords);
+  w.hbits = R <= kHashRMax ? hash_bits(R) : 0;
+  int64_t buckets = 0;
+  if (w.hbits) {
+    const size_t slots = (size_t)1 << w.hbits;
+    buckets = (int64_t)1 << bucket_bits(w.hbits);
+    w.hk = (unsigned long long *)p; p += align_up(8 * slots);
+    w.hfirst = (uint32_t *)p; p += align_up(4 * (slots + 1));
+    w.hcnt = (uint32_t *)p; p += align_up(4 * (slots + 1));
+    w.hgid = (int32_t *)p; p += align_up(4 * (slots + 1));
+    w.bcnt = (uint32_t *)p; p += align_up(4 * buckets);
+    w.bkey = (uint64_t *)p; p += align_up(8 * buckets * kBucketCap);
+    w.bslot = (int32_t *)p;
+  }
   int Ri = (int)R;
   const int64_t chunks = (R + kPrepChunk - 1) / kPrepChunk;
   const int P = chunks < kPrepMax ? (int)chunks : kPrepMax;
@@ -932,7 +1205,8 @@ hipError_t launch_dedup(const int64_t *keys, int64_t R, int64_t *uk, int32_t *fi
   if (rounds > 4096) rounds = 4096;
   hipLaunchKernelGGL(dense_mark_kernel, dim3((unsigned)rounds), dim3(kRadixThreads), 0, st, Ri,
                      P, w);
-  hipLaunchKernelGGL(dense_groups_kernel, dim3((unsigned)nvb), dim3(kRadixThreads), 0, st, Ri,
+  // (a workgroup per value block or per bucket)
+  hipLaunchKernelGGL(dense_groups_kernel, dim3((unsigned)(nvb > buckets ? nvb : buckets)), dim3(kRadixThreads), 0, st, Ri,
                      w, uk, fi, cnt, nu);
   int64_t ib = (R + 255) / 256;
   if (ib > 8192) ib = 8192;

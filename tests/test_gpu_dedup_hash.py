@@ -1,0 +1,80 @@
+"""Dedup of wide-range keys through the hash table, and its edges: the smallest
+and largest request counts of the path, the key that maps to the empty mark
+(INT64_MIN), hot keys, keys that fill one bucket (left to the sort) and keys
+whose first 1,024 lie close together (never hashed)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_harness import device, note, to_dev
+
+pytestmark = pytest.mark.gpu
+
+I64 = np.iinfo(np.int64)
+
+
+def _check(keys, runs=2):
+    import paper_2607_22578_amd as hs
+    dev = device()
+    R = keys.shape[0]
+    plan = hs.hs_merge_plan(R, 8, 1, 1, hs.HS_BF16, hs.HS_BF16)
+    ws = torch.full((plan.workspace_bytes,), 0xA5, dtype=torch.uint8, device=dev)
+    out = [torch.empty(R, dtype=t, device=dev)
+           for t in (torch.int64, torch.int32, torch.int32, torch.int32)]
+    nu_dev = torch.zeros(1, dtype=torch.int64, device=dev)
+    kd = to_dev(keys)
+    ref = oracle.dedup(keys)
+    for _ in range(runs):   # the second run finds the first one's scratch
+        for t in out:
+            t.fill_(-7)
+        nu = hs.hs_dedup(plan, kd, *out, nu_dev, True, ws)
+        torch.cuda.synchronize()
+        assert nu == ref["n_unique"]
+        for t, name in zip(out, ("unique_keys", "first_index", "counts")):
+            np.testing.assert_array_equal(t[:nu].cpu().numpy(), ref[name], err_msg=name)
+        np.testing.assert_array_equal(out[3].cpu().numpy(), ref["inverse"])
+
+
+def _uniform(rng, n):
+    return rng.integers(I64.min, I64.max, size=n, endpoint=True)
+
+
+@pytest.mark.parametrize("R,pool", [(4_097, 4_097), (4_097, 3), (8_192, 5_000), (8_193, 700),
+                                    (65_537, 60_000), (200_000, 90_000), (1 << 20, 400_000),
+                                    ((1 << 20) + 1, 400_000)])
+def test_uniform_keys(R, pool):
+    note(f"dedup hash R={R} pool={pool}")
+    rng = np.random.default_rng(R + pool)
+    pool_keys = _uniform(rng, pool)
+    _check(pool_keys[rng.integers(0, pool, size=R)])
+
+
+def test_extreme_keys_and_hot_keys():
+    rng = np.random.default_rng(5)
+    keys = _uniform(rng, 30_000)
+    keys[rng.random(30_000) < 0.3] = I64.min       # maps to the empty mark
+    keys[rng.random(30_000) < 0.3] = I64.max
+    keys[rng.random(30_000) < 0.1] = 0
+    _check(keys)
+
+
+@pytest.mark.parametrize("kind", ["clustered", "few outliers", "late range", "all equal but one"])
+def test_keys_the_table_does_not_suit(kind):
+    # clustered: two runs of consecutive keys far apart fill two buckets, so
+    # the hash path gives up and the sort runs; late range: the first 1,024
+    # keys are close together, so the sort runs at once
+    rng = np.random.default_rng(6)
+    n = 20_000
+    if kind == "clustered":
+        keys = rng.integers(0, 9_000, size=n) + rng.integers(0, 2, size=n) * (1 << 60)
+    elif kind == "few outliers":
+        keys = rng.integers(0, 50_000, size=n)
+        keys[::1_000] = _uniform(rng, keys[::1_000].size)
+    elif kind == "late range":
+        keys = _uniform(rng, n)
+        keys[:1_024] = 17
+    else:
+        keys = np.full(n, 3, dtype=np.int64)
+        keys[0] = I64.max
+    _check(keys.astype(np.int64))
