@@ -7,14 +7,12 @@
 // of (key, request) pairs): distinct keys ascending, the survivor of a group
 // is its earliest request, counts[g] = |M(v*)|, inverse[i] = group.
 //
-// Three paths:
-//   R <= kHashMax  : one workgroup groups the keys in an LDS hash table
+// Paths:
+//   R <= kSmallMax : one workgroup groups the keys in an LDS hash table
 //                    (first request by atomic min, group size by atomic add),
 //                    orders the distinct keys by counting, for each, the
-//                    distinct keys below it, and maps every request to its
-//                    group through the table;
-//   R <= kSmallMax : one workgroup sorts (key, idx) in LDS with a bitonic
-//                    network and compacts in the same launch;
+//                    distinct keys below it (in its bucket of the key range),
+//                    and maps every request to its group through the table;
 //   larger R       : the key range is found on the device; keys that take at
 //                    most R values are grouped by direct addressing over the
 //                    range; keys spread over a wide range (signatures) by a
@@ -73,193 +71,169 @@ __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t *w
   return r;
 }
 
-// ---------------------------------------------------------------- small R
+// ---------------------------------------------------------------- up to 4,096
 
-__global__ __launch_bounds__(kSmallThreads) void dedup_small_kernel(
-    const int64_t *__restrict__ keys, int R, int P, int64_t *__restrict__ uk,
-    int32_t *__restrict__ fi, int32_t *__restrict__ cnt, int32_t *__restrict__ inv,
-    int64_t *__restrict__ nu_out) {
-  __shared__ uint64_t sk[kSmallMax];
-  __shared__ int32_t si[kSmallMax];
-  __shared__ uint32_t wsum[kSmallThreads / 64 + 1];
-  const int tid = threadIdx.x;
-  for (int p = tid; p < P; p += kSmallThreads) {
-    if (p < R) {
-      sk[p] = map_key(keys[p]);
-      si[p] = p;
-    } else {  // padding sorts after every real (key, idx) pair
-      sk[p] = ~0ull;
-      si[p] = 0x7FFFFFFF;
-    }
-  }
-  __syncthreads();
-  // bitonic sort of (key, idx) ascending
-  for (int size = 2; size <= P; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int t = tid; t < (P >> 1); t += kSmallThreads) {
-        int i = 2 * t - (t & (stride - 1));
-        int j = i + stride;
-        bool up = (i & size) == 0;
-        uint64_t ki = sk[i], kj = sk[j];
-        int32_t ii = si[i], ij = si[j];
-        bool gt = ki > kj || (ki == kj && ii > ij);
-        if (gt == up) {
-          sk[i] = kj; sk[j] = ki;
-          si[i] = ij; si[j] = ii;
-        }
-      }
-      __syncthreads();
-    }
-  }
-  // heads and group ids: thread t owns positions [t*E, t*E + E)
-  constexpr int E = kSmallMax / kSmallThreads;
-  int64_t myk[E];
-  int32_t myi[E];
-  bool head[E];
-  uint32_t h = 0;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    int p = tid * E + e;
-    myk[e] = 0;
-    myi[e] = 0;
-    head[e] = false;
-    if (p < R) {
-      myk[e] = unmap_key(sk[p]);
-      myi[e] = si[p];
-      head[e] = (p == 0) || (sk[p] != sk[p - 1]);
-      h += head[e];
-    }
-  }
-  uint32_t total;
-  uint32_t incl = block_inclusive_scan<kSmallThreads>(h, wsum, total);
-  uint32_t g = incl - h;  // heads before this thread
-  // si is free now: reuse it for group start positions
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    int p = tid * E + e;
-    if (p < R) {
-      if (head[e]) {
-        uk[g] = myk[e];
-        fi[g] = myi[e];
-        si[g] = p;
-        ++g;
-      }
-      inv[myi[e]] = (int32_t)(g - 1);
-    }
-  }
-  __syncthreads();
-  if (cnt) {
-    for (int q = tid; q < (int)total; q += kSmallThreads) {
-      int end = (q + 1 < (int)total) ? si[q + 1] : R;
-      cnt[q] = end - si[q];
-    }
-  }
-  if (tid == 0) *nu_out = (int64_t)total;
-}
+constexpr int kRankDirect = 512;     // distinct keys ranked over all of them up to here
+constexpr int kRankBuckets = 512;    // buckets of the key range above
 
-// ---------------------------------------------------------------- hash path
-
-constexpr int kHashMax = 2048;
-constexpr int kHashSlots = 2 * kHashMax;   // load factor at most 1/2
-constexpr int kHashPer = kHashMax / kSmallThreads;
-
+// One workgroup; RMAX requests at most, in a table of twice as many slots.
+// Bound by latency: a few barriers, and the ranking.  Ranking every distinct key
+// by counting all of them takes n^2 LDS reads: 1.2 us of the 9 us for 329
+// keys, but most of the time from about a thousand.  Above kRankDirect, the keys
+// are first put into kRankBuckets buckets of their range, and a key counts only
+// those of its bucket (with keys in few buckets, as many reads as before).
+// 3,000 requests, 960 distinct: 56 us by a bitonic sort of the requests.
+template <int RMAX>
 __global__ __launch_bounds__(kSmallThreads) void dedup_hash_kernel(
     const int64_t *__restrict__ keys, int R, int64_t *__restrict__ uk, int32_t *__restrict__ fi,
     int32_t *__restrict__ cnt, int32_t *__restrict__ inv, int64_t *__restrict__ nu_out) {
   // Mapped keys (map_key: order-preserving to unsigned) in open addressing
   // with linear probing; mapped value 0 marks an empty slot, so the one key
-  // that maps to 0 (INT64_MIN) is counted in a group of its own (zmin, zcnt).
-  __shared__ unsigned long long hk[kHashSlots];
-  __shared__ int32_t hmin[kHashSlots];   // first request; later the group id
-  __shared__ int32_t hcnt[kHashSlots];
-  __shared__ unsigned long long ck[kHashMax + 8];   // distinct mapped keys
-  __shared__ int32_t cslot[kHashMax + 1];           // their slots (-1: key 0)
-  __shared__ int32_t ncomp, zmin, zcnt, zgroup;
+  // that maps to 0 (INT64_MIN) has a slot of its own, number SLOTS.
+  constexpr int SLOTS = 2 * RMAX;    // load factor at most 1/2
+  constexpr int PER = RMAX / kSmallThreads;
+  __shared__ unsigned long long hk[SLOTS + 1];
+  __shared__ int32_t hmin[SLOTS + 1];   // first request; later the group id
+  __shared__ int32_t hcnt[SLOTS + 1];
+  __shared__ uint16_t order[RMAX];      // slots of the distinct keys
+  __shared__ unsigned long long ck[kRankDirect + 8];   // distinct keys, up to kRankDirect
+  __shared__ uint32_t bcnt[kRankBuckets], bat[kRankBuckets];
+  __shared__ uint64_t smin[kSmallThreads / 64], smax[kSmallThreads / 64];
+  __shared__ uint32_t wsum[kSmallThreads / 64 + 1];
+  __shared__ int32_t ncomp;
   const int tid = threadIdx.x;
-  for (int t = tid; t < kHashSlots; t += kSmallThreads) {
+  for (int t = tid; t <= SLOTS; t += kSmallThreads) {
     hk[t] = 0ull;
     hmin[t] = 0x7FFFFFFF;
     hcnt[t] = 0;
   }
-  if (tid == 0) {
-    ncomp = 0;
-    zmin = 0x7FFFFFFF;
-    zcnt = 0;
-  }
+  if (tid < kRankBuckets) bcnt[tid] = 0u;
+  if (tid == 0) ncomp = 0;
   __syncthreads();
-  int myslot[kHashPer];
+  int myslot[PER];
 #pragma unroll
-  for (int e = 0; e < kHashPer; ++e) {
+  for (int e = 0; e < PER; ++e) {
     const int p = tid + e * kSmallThreads;
     myslot[e] = -1;
     if (p < R) {
       const unsigned long long m = map_key(keys[p]);
-      if (m == 0ull) {
-        atomicMin(&zmin, p);
-        atomicAdd(&zcnt, 1);
-      } else {
-        uint32_t sl = (uint32_t)((m * 0x9E3779B97F4A7C15ull) >> 52) & (kHashSlots - 1);
+      uint32_t sl = SLOTS;
+      if (m != 0ull) {
+        sl = (uint32_t)((m * 0x9E3779B97F4A7C15ull) >> 51) & (SLOTS - 1);
         for (;;) {   // at most R probes: fewer keys than slots
           const unsigned long long prev = atomicCAS(&hk[sl], 0ull, m);
           if (prev == 0ull || prev == m) break;
-          sl = (sl + 1) & (kHashSlots - 1);
+          sl = (sl + 1) & (SLOTS - 1);
         }
-        atomicMin(&hmin[sl], p);
-        atomicAdd(&hcnt[sl], 1);
-        myslot[e] = (int)sl;
       }
+      atomicMin(&hmin[sl], p);
+      atomicAdd(&hcnt[sl], 1);
+      myslot[e] = (int)sl;
     }
   }
   __syncthreads();
-  // distinct keys in slot order
-  for (int t = tid; t < kHashSlots; t += kSmallThreads) {
-    if (hk[t] != 0ull) {
+  // distinct keys in any order (one slot per distinct key holds requests)
+  uint64_t mn = ~0ull, mx = 0ull;
+  for (int t = tid; t <= SLOTS; t += kSmallThreads) {
+    if (hcnt[t] != 0) {
       const int u = atomicAdd(&ncomp, 1);
-      ck[u] = hk[t];
-      cslot[u] = t;
+      const uint64_t m = hk[t];
+      order[u] = (uint16_t)t;
+      if (u < kRankDirect) ck[u] = m;
+      mn = m < mn ? m : mn;
+      mx = m > mx ? m : mx;
     }
-  }
-  __syncthreads();
-  if (tid == 0 && zcnt > 0) {
-    ck[ncomp] = 0ull;
-    cslot[ncomp] = -1;
-    ++ncomp;
   }
   __syncthreads();
   const int n = ncomp;
-  // group id = number of distinct keys below (keys are distinct); the list
-  // is padded to a multiple of 8 with all-ones keys (never below a key) so
-  // that eight independent reads are in flight at a time
-  const int n8 = (n + 7) & ~7;
-  for (int u = n + tid; u < n8; u += kSmallThreads) ck[u] = ~0ull;
-  __syncthreads();
-  for (int u = tid; u < n; u += kSmallThreads) {
-    const unsigned long long m = ck[u];
-    int r = 0;
-    for (int j = 0; j < n8; j += 8) {
-      unsigned long long b[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) b[t] = ck[j + t];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) r += b[t] < m ? 1 : 0;
-    }
-    const int sl = cslot[u];
+  auto put = [&](int sl, uint64_t m, int r) {
     uk[r] = unmap_key(m);
-    if (sl >= 0) {
-      fi[r] = hmin[sl];
-      if (cnt) cnt[r] = hcnt[sl];
-      hmin[sl] = r;   // (this thread is the only one that reads the slot here)
-    } else {
-      fi[r] = zmin;
-      if (cnt) cnt[r] = zcnt;
-      zgroup = r;
+    fi[r] = hmin[sl];
+    if (cnt) cnt[r] = hcnt[sl];
+    hmin[sl] = r;   // (this thread is the only one that reads the slot here)
+  };
+  if (n <= kRankDirect) {
+    // group id = number of distinct keys below (keys are distinct); the list
+    // is padded to a multiple of 8 with all-ones keys (never below a key) so
+    // that eight independent reads are in flight at a time
+    const int n8 = (n + 7) & ~7;
+    if (tid < n8 - n) ck[n + tid] = ~0ull;
+    __syncthreads();
+    if (tid < n) {
+      const unsigned long long m = ck[tid];
+      int r = 0;
+      for (int j = 0; j < n8; j += 8) {
+        unsigned long long b[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) b[t] = ck[j + t];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) r += b[t] < m ? 1 : 0;
+      }
+      put(order[tid], m, r);
+    }
+  } else {
+    for (int o = 32; o > 0; o >>= 1) {
+      const uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
+      mn = a < mn ? a : mn;
+      mx = c > mx ? c : mx;
+    }
+    if ((tid & 63) == 0) {
+      smin[tid >> 6] = mn;
+      smax[tid >> 6] = mx;
+    }
+    __syncthreads();
+    mn = smin[0];
+    mx = smax[0];
+    for (int w = 1; w < kSmallThreads / 64; ++w) {
+      mn = smin[w] < mn ? smin[w] : mn;
+      mx = smax[w] > mx ? smax[w] : mx;
+    }
+    // bucket = the top 9 bits of the range's key - min
+    const int bits = 64 - __clzll((long long)(mx - mn));   // (n > 1: mx > mn)
+    const int shift = bits > 9 ? bits - 9 : 0;
+    int msl[PER];
+    uint32_t mb[PER], mat[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int u = tid + e * kSmallThreads;
+      msl[e] = u < n ? (int)order[u] : -1;
+      if (u < n) {
+        mb[e] = (uint32_t)((hk[msl[e]] - mn) >> shift);
+        mat[e] = atomicAdd(&bcnt[mb[e]], 1u);
+      }
+    }
+    __syncthreads();
+    uint32_t total;
+    const uint32_t c = tid < kRankBuckets ? bcnt[tid] : 0u;
+    const uint32_t incl = block_inclusive_scan<kSmallThreads>(c, wsum, total);
+    if (tid < kRankBuckets) bat[tid] = incl - c;
+    __syncthreads();
+    // (every thread has read its entries of `order`)
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (msl[e] >= 0) order[bat[mb[e]] + mat[e]] = (uint16_t)msl[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      if (msl[e] < 0) continue;
+      const uint64_t m = hk[msl[e]];
+      const int b0 = (int)bat[mb[e]], b1 = b0 + (int)bcnt[mb[e]];
+      int r = b0;
+      for (int j = b0; j < b1; j += 4) {
+        uint64_t y[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) y[t] = j + t < b1 ? hk[order[j + t]] : ~0ull;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r += y[t] < m ? 1 : 0;
+      }
+      put(msl[e], m, r);
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < kHashPer; ++e) {
+  for (int e = 0; e < PER; ++e) {
     const int p = tid + e * kSmallThreads;
-    if (p < R) inv[p] = myslot[e] >= 0 ? hmin[myslot[e]] : zgroup;
+    if (p < R) inv[p] = hmin[myslot[e]];
   }
   if (tid == 0) *nu_out = (int64_t)n;
 }
@@ -1152,17 +1126,10 @@ static int radix_capacity() {
 
 hipError_t launch_dedup(const int64_t *keys, int64_t R, int64_t *uk, int32_t *fi, int32_t *cnt,
                         int32_t *inv, int64_t *nu, void *ws, hipStream_t st) {
-  if (R <= kHashMax) {
-    hipLaunchKernelGGL(dedup_hash_kernel, dim3(1), dim3(kSmallThreads), 0, st, keys, (int)R, uk,
-                       fi, cnt, inv, nu);
-    return hipGetLastError();
-  }
   if (R <= kSmallMax) {
-    int P = 1;
-    while (P < R) P <<= 1;
-    if (P < 2) P = 2;
-    hipLaunchKernelGGL(dedup_small_kernel, dim3(1), dim3(kSmallThreads), 0, st, keys, (int)R,
-                       P, uk, fi, cnt, inv, nu);
+    hipLaunchKernelGGL(R <= kSmallMax / 2 ? dedup_hash_kernel<kSmallMax / 2>
+                                          : dedup_hash_kernel<kSmallMax>,
+                       dim3(1), dim3(kSmallThreads), 0, st, keys, (int)R, uk, fi, cnt, inv, nu);
     return hipGetLastError();
   }
   const int capacity = radix_capacity();

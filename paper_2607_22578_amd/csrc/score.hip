@@ -29,13 +29,21 @@ constexpr int kMergeThreads = 1024;
 constexpr int kMergeRankMax = 2048;   // survivors ranked by counting up to this many
 
 // One workgroup per distinct query.  Its S*k slice keys are compacted into
-// LDS, dropping empty keys, keys below the k-th largest list head when the
-// lists are sorted, and, when a shared threshold is given, keys whose score
-// is below it (each a lower bound of the query's k-th best, so every key of
-// the final k survives); the survivors are sorted (bitonic,
-// descending; up to kMergeRankMax survivors are ranked by counting the
-// survivors above each instead) and the first k decoded to (score, row),
+// LDS, dropping empty keys, keys below the cut, and, when a shared threshold is
+// given, keys whose score is below it (each a lower bound of the query's k-th
+// best, so every key of the final k survives); the survivors are sorted
+// (bitonic, descending; up to kMergeRankMax survivors are ranked by counting
+// the survivors above each instead) and the first k decoded to (score, row),
 // ranks past the survivors padded with (-inf, -1).
+//
+// The cut, from the slices' sorted lists: if r lists hold ceil(k / r) keys of
+// at least x each, then k distinct rows do, so the r-th largest of the lists'
+// ceil(k / r)-th keys is a lower bound of the k-th best key, as is the k-th
+// largest list head when S >= k.  The heads alone leave few survivors when
+// there are many more lists than k; with fewer than 4 k lists, the largest
+// bound over r = 1, 2, 4, ... is taken (up to kMergeThreads values in all).
+// Ranking takes m^2 LDS reads for m survivors: 960 queries, k = 50, S = 32 had
+// about a thousand with the shared threshold alone, 109 us.
 __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
     const uint64_t *__restrict__ part, const uint32_t *__restrict__ thr, int64_t n_unique,
     const int64_t *__restrict__ n_unique_dev, int64_t cap, int64_t N, int k, int mq, int nc,
@@ -55,18 +63,30 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
       count = 0;
       head_cut = 0ull;
     }
-    // With lists sorted in descending order, the k-th largest of the S list
-    // heads is also a lower bound of the query's k-th best key: the heads
-    // are keys of distinct rows (empty heads are 0 and tie, leaving the cut
-    // at 0 when fewer than k slices kept anything).
-    const bool use_heads = sp.S >= k && sp.S <= kMergeThreads;
-    if (use_heads && tid < sp.S) heads[tid] = src[(int64_t)tid * k];
+    // level l: r = 2^l lists and their ceil(k / r)-th keys; the last level
+    // is that of the heads, where there are k
+    const int S = (int)sp.S;
+    int levels = 0, first = 0;
+    if (S <= kMergeThreads) {
+      int below = 0;   // levels with r < k, r <= S
+      while ((1 << below) < k && (1 << below) <= S) ++below;
+      levels = below + (S >= k ? 1 : 0);
+      first = S >= 4 * k ? levels - 1 : levels * S > kMergeThreads ? levels - kMergeThreads / S : 0;
+    }
+    const bool at = tid < (levels - first) * S;
+    const int l = at ? first + tid / S : 0;
+    const int r_l = 1 << l >= k ? k : 1 << l;
+    uint64_t hk = 0ull;
+    if (at) {
+      hk = src[(int64_t)(tid % S) * k + (k + r_l - 1) / r_l - 1];
+      heads[tid] = hk;
+    }
     __syncthreads();
-    if (use_heads && tid < sp.S) {
-      const uint64_t hk = heads[tid];
+    if (hk != 0ull) {
+      const uint64_t *hl = heads + (l - first) * S;
       int r = 0;
-      for (int j = 0; j < (int)sp.S; ++j) r += heads[j] > hk ? 1 : 0;
-      if (r == k - 1 && hk != 0ull) head_cut = hk;
+      for (int j = 0; j < S; ++j) r += hl[j] > hk ? 1 : 0;
+      if (r == r_l - 1) atomicMax((unsigned long long *)&head_cut, (unsigned long long)hk);
     }
     __syncthreads();
     const uint64_t cut = head_cut;

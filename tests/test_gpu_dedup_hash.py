@@ -78,3 +78,19 @@ def test_keys_the_table_does_not_suit(kind):
         keys = np.full(n, 3, dtype=np.int64)
         keys[0] = I64.max
     _check(keys.astype(np.int64))
+
+
+@pytest.mark.parametrize("R", [513, 600, 2_047, 2_048, 2_049, 3_000, 4_096])
+@pytest.mark.parametrize("kind", ["uniform", "dense", "one bucket"])
+def test_one_workgroup_ranking(R, kind):
+    # up to 512 distinct keys are ranked directly, more by buckets of the range;
+    # "one bucket": all but two keys in the range's lowest bucket
+    rng = np.random.default_rng(R)
+    keys = _uniform(rng, R)
+    if kind == "dense":
+        keys = rng.permutation(R).astype(np.int64) - 5
+    elif kind == "one bucket":
+        keys = rng.permutation(R).astype(np.int64)
+        keys[:2] = I64.min, I64.max
+    _check(keys)
+    _check(keys[rng.integers(0, R, size=R)], runs=1)
