@@ -27,6 +27,7 @@ constexpr int kGridMax = 512;       // persistent grid never exceeds this
 
 constexpr int kMergeThreads = 1024;
 constexpr int kMergeRankMax = 2048;   // survivors ranked by counting up to this many
+constexpr int kMergeCutMin = 512;     // as many keys are ranked as soon as cut
 
 // One workgroup per distinct query.  Its S*k slice keys are compacted into
 // LDS, dropping empty keys, keys below the cut, and, when a shared threshold is
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
     // is that of the heads, where there are k
     const int S = (int)sp.S;
     int levels = 0, first = 0;
-    if (S <= kMergeThreads) {
+    if (S <= kMergeThreads && n > kMergeCutMin) {
       int below = 0;   // levels with r < k, r <= S
       while ((1 << below) < k && (1 << below) <= S) ++below;
       levels = below + (S >= k ? 1 : 0);
