@@ -80,22 +80,47 @@ constexpr int kMVals = 16 * kMRB;        // scores per lane and query per tile
 constexpr int kMLanesQ = kMW * 2;        // lanes holding one query in a tile
 
 // Seed pass sample: the lane maxima of the first T tiles of every slice (at
-// most kSeedMax of them per query).  T is one for k <= 48.  For larger k the
-// k-th largest lane maximum of one tile per slice is a weak bound (k is then a
-// sizeable fraction of the sample): a sample of M rows lets about N k / M rows
-// of the corpus pass it, each a list insertion, and with many slices the
-// lists do not fill before their slice ends, so their own minima never take
-// over.  T therefore grows to 20 as long as the sample stays within 1/16 of
-// the slice's tiles and within kSeedMax values.
+// most kSeedMax of them per query).
+//
+// A sample of M = 384 S T rows lets about N k / M rows of the corpus pass its
+// bound, each an insertion into a list, while every sampled tile is computed
+// twice.
+// - Short slices (n < 4 S, n = tiles per slice): the list of a slice of n rows
+//   hardly ever bounds better than the seed of T S, so a workgroup's 128
+//   queries take in proportion to k n / (S T) insertions, and T tiles of nch
+//   stages plus the maxima (about 1.6 stages): T^2 = c k n / (S (nch + 1.6)).
+//   c = 6, measured: 960 queries, 500,009 x 400 fp8, k = 50 (n = 40, S = 32),
+//   seed pass + selection + main pass: T = 2 (as before) 1,042 us, c = 6 (T =
+//   7) 805, c = 12 811, c = 25 827, c = 50 904; 329 queries, 1M x 768 bf16, k =
+//   10 (n = 30, S = 85): T = 1 (c = 6) 709 us, T = 2 715; 336 queries, 333,333
+//   x 1,000, k = 20 (n = 10, S = 85): T = 1 430 us, T = 2 447.
+// - Longer slices: their own lists and the bounds they publish take over.  One
+//   tile for k <= 48 (8 or 16 changed nothing at k = 32, n = 651, S = 16); for
+//   larger k the lists fill late, and T grows to 20 within 1/16 of the slice.
 constexpr int kSeedMax = 16384;
 constexpr int kSeedTilesMax = 20;
-__host__ __device__ __forceinline__ int seed_tiles(int k, int64_t ntiles, int64_t S) {
-  if (k <= 48 || S < 1) return 1;
-  int64_t t = ntiles / (S * 16);
-  const int64_t room = kSeedMax / (S * kMLanesQ);
+// the most for any shape (the maxima share the lists' bytes: 32 T against 8 k
+// bytes per query and slice)
+__host__ __device__ __forceinline__ int seed_tiles_max(int k) {
+  return k > 48 ? kSeedTilesMax : k < 8 ? 1 : k / 4;
+}
+__host__ __device__ __forceinline__ int seed_tiles(int k, int64_t ntiles, int64_t S, int nch) {
+  if (S < 1) return 1;
+  const int n = (int)(ntiles / S);
+  int t = 1;
+  if (n < 4 * S) {
+    // the integer whose square is nearest below twice-rounded T^2 (no square
+    // root: host and device must agree)
+    const int64_t num = 60 * (int64_t)k * n, den = S * (10 * (int64_t)nch + 16);
+    while (t < kSeedTilesMax && (int64_t)(2 * t + 1) * (2 * t + 1) * den <= 4 * num) ++t;
+    if (t > n / 2) t = n / 2;
+  } else if (k > 48) {
+    t = n / 16;
+  }
+  const int room = (int)(kSeedMax / (S * kMLanesQ));
   if (t > room) t = room;
-  if (t > kSeedTilesMax) t = kSeedTilesMax;
-  return t < 1 ? 1 : (int)t;
+  if (t > seed_tiles_max(k)) t = seed_tiles_max(k);
+  return t < 1 ? 1 : t;
 }
 // Slices that take part in the seed sample: one in every seed_stride(S), at
 // most kSeedSlices of them.  A single query tile runs as up to 256 slices, and
@@ -692,7 +717,7 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
     const int qt = w % (int)sp.qtiles;
     it.s = w / (int)sp.qtiles;
     it.S = sp.S;
-    it.T = seed_tiles(a.k, sp.ntiles, sp.S);
+    it.T = seed_tiles(a.k, sp.ntiles, sp.S, nch);
     const int s0 = (int)((int64_t)it.s * sp.ntiles / sp.S);
     const int s1 = (int)((int64_t)(it.s + 1) * sp.ntiles / sp.S);
     const int t0 = s0;
@@ -1059,8 +1084,8 @@ int persistent_grid();
 // (rounded to 256 bytes) followed by the partial lists.
 size_t mfma_thr_bytes(int64_t cap) { return ((size_t)cap * 4 + 255) & ~(size_t)255; }
 
-// worst case over n_u in [1, cap] and grids up to grid_max of n_u * S * f(k),
-// f(k) = per_slice bytes, times the seed pass's tiles per slice if seed.
+// worst case over n_u in [1, cap] and grids up to grid_max of n_u * S *
+// per_slice bytes.
 // It takes up to (cap / 128) x 64 splits, and every score call lays out its
 // workspace with it, so results are kept for the few shapes a process uses
 // (on a window of a few hundred queries the loops cost tens of microseconds,
@@ -1069,20 +1094,19 @@ struct SplitWorstMemo {
   int64_t cap, N;
   int k, grid_max;
   size_t per_slice;
-  bool seed, valid;
+  bool valid;
   size_t bytes;
 };
 static std::mutex g_split_memo_mu;
 static SplitWorstMemo g_split_memo[16];
 static unsigned g_split_memo_next = 0;
 
-static size_t mfma_split_worst(int64_t cap, int64_t N, int k, int grid_max, size_t per_slice,
-                               bool seed = false) {
+static size_t mfma_split_worst(int64_t cap, int64_t N, int k, int grid_max, size_t per_slice) {
   {
     std::lock_guard<std::mutex> lock(g_split_memo_mu);
     for (const SplitWorstMemo &m : g_split_memo)
       if (m.valid && m.cap == cap && m.N == N && m.k == k && m.grid_max == grid_max &&
-          m.per_slice == per_slice && m.seed == seed)
+          m.per_slice == per_slice)
         return m.bytes;
   }
   size_t best = 0;
@@ -1093,40 +1117,34 @@ static size_t mfma_split_worst(int64_t cap, int64_t N, int k, int grid_max, size
     const int64_t nu = qt * kMMQ < cap ? qt * kMMQ : cap;
     for (int64_t g = 8; g <= grid_max; g += 8) {
       const Split sp = make_split(nu, N, kMMQ, kMNC, g, smax);
-      const size_t b = (size_t)nu * (size_t)sp.S * per_slice *
-                       (seed ? (size_t)seed_tiles(k, sp.ntiles, sp.S) : 1u);
+      const size_t b = (size_t)nu * (size_t)sp.S * per_slice;
       if (b > best) best = b;
     }
   }
   best = (best + 255) & ~(size_t)255;
   std::lock_guard<std::mutex> lock(g_split_memo_mu);
-  g_split_memo[g_split_memo_next++ % 16] = {cap, N, k, grid_max, per_slice, seed, true, best};
+  g_split_memo[g_split_memo_next++ % 16] = {cap, N, k, grid_max, per_slice, true, best};
   return best;
 }
 
 // Score workspace of the matrix-core path: [shared thresholds, cap x u32 |
-// seed-pass lane maxima, n_u x S x T x 8 u32 | order statistics of finished
-// items, n_u x kLvl x S u32 | partial lists, n_u x S x k keys],
-// each rounded to 256 bytes.
-size_t mfma_lmax_bytes(int64_t cap, int64_t N, int k, int grid_max) {
-  return mfma_split_worst(cap, N, k, grid_max, (size_t)kMLanesQ * 4, true);
-}
-
+// order statistics of finished items, n_u x kLvl x S u32 | partial lists, n_u
+// x S x k keys, and before them in the same bytes the seed pass's lane maxima,
+// n_u x S x T x 8 u32], each rounded to 256 bytes.
 // published order statistics, n_u x S x kLvl u32
 static size_t mfma_lvl_bytes(int64_t cap, int64_t N, int k, int grid_max) {
   return mfma_split_worst(cap, N, k, grid_max, (size_t)kLvl * 4);
 }
 
-size_t mfma_partial_bytes(int64_t cap, int64_t N, int k, int grid_max) {
-  return mfma_thr_bytes(cap) + mfma_lmax_bytes(cap, N, k, grid_max) +
-         mfma_lvl_bytes(cap, N, k, grid_max) +
-         mfma_split_worst(cap, N, k, grid_max, (size_t)k * 8);
+// Offset of the partial lists (and the lane maxima) in the score workspace.
+size_t mfma_part_offset(int64_t cap, int64_t N, int k, int grid_max) {
+  return mfma_thr_bytes(cap) + mfma_lvl_bytes(cap, N, k, grid_max);
 }
 
-// Offset of the partial lists in the score workspace.
-size_t mfma_part_offset(int64_t cap, int64_t N, int k, int grid_max) {
-  return mfma_thr_bytes(cap) + mfma_lmax_bytes(cap, N, k, grid_max) +
-         mfma_lvl_bytes(cap, N, k, grid_max);
+size_t mfma_partial_bytes(int64_t cap, int64_t N, int k, int grid_max) {
+  const size_t lists = (size_t)k * 8, maxima = (size_t)seed_tiles_max(k) * kMLanesQ * 4;
+  return mfma_part_offset(cap, N, k, grid_max) +
+         mfma_split_worst(cap, N, k, grid_max, lists > maxima ? lists : maxima);
 }
 
 void mfma_split_params(int *mq, int *nc, int64_t *smax, int k) {
@@ -1158,7 +1176,7 @@ constexpr int kSeedThreads = 256;
 template <bool F32>
 __global__ __launch_bounds__(kSeedThreads) void mfma_seed_kernel(
     const uint32_t *__restrict__ lmax, int64_t n_unique, const int64_t *__restrict__ nu_dev,
-    int64_t cap, int64_t N, int k, int64_t smax, int grid, uint32_t *__restrict__ gthr,
+    int64_t cap, int64_t N, int nch, int k, int64_t smax, int grid, uint32_t *__restrict__ gthr,
     uint32_t *__restrict__ lvl) {
   __shared__ uint32_t vals[kSeedMax];
   __shared__ uint32_t hist[256];
@@ -1170,7 +1188,7 @@ __global__ __launch_bounds__(kSeedThreads) void mfma_seed_kernel(
     const int64_t stride = f32_seed_stride(sp.S);
     per = f32_seeded(sp) ? (sp.S + stride - 1) / stride * kFGroups : 0;
   } else {
-    per = sp.S * kMLanesQ * seed_tiles(k, sp.ntiles, sp.S);
+    per = sp.S * kMLanesQ * seed_tiles(k, sp.ntiles, sp.S, nch);
   }
   const int n = (int)(per < kSeedMax ? per : kSeedMax);
   const int tid = threadIdx.x;
@@ -1244,7 +1262,8 @@ hipError_t launch_seed_select(const MfmaArgs &a, int64_t smax, bool f32, hipStre
   if (blocks <= 0) return hipSuccess;
   hipLaunchKernelGGL(f32 ? mfma_seed_kernel<true> : mfma_seed_kernel<false>,
                      dim3((unsigned)blocks), dim3(kSeedThreads), 0, st, a.lmax, a.n_unique,
-                     a.n_unique_dev, a.cap, a.N, a.k, smax, a.grid, a.gthr, a.lvl);
+                     a.n_unique_dev, a.cap, a.N, (int)((a.d + kMKC - 1) / kMKC), a.k, smax, a.grid,
+                     a.gthr, a.lvl);
   return hipGetLastError();
 }
 
@@ -1361,10 +1380,9 @@ hipError_t launch_score_mfma(const void *q, const void *corpus, const float *sca
                              int64_t cap, bool fp8, bool tiled, void *ws, hipStream_t st) {
   // shared thresholds: (re)started by the seed selection on every call
   uint32_t *gthr = (uint32_t *)ws;
-  uint32_t *lmax = (uint32_t *)((unsigned char *)ws + mfma_thr_bytes(cap));
-  uint32_t *lvl = (uint32_t *)((unsigned char *)ws + mfma_thr_bytes(cap) +
-                               mfma_lmax_bytes(cap, N, k, kMGridMax));
+  uint32_t *lvl = (uint32_t *)((unsigned char *)ws + mfma_thr_bytes(cap));
   void *part = (unsigned char *)ws + mfma_part_offset(cap, N, k, kMGridMax);
+  uint32_t *lmax = (uint32_t *)part;
   void *qt = (unsigned char *)ws + mfma_qtile_offset(cap, N, k, kMGridMax);
   hipError_t e = launch_tile_queries(q, n_unique, nu_dev, cap, d * 2, qt, st);
   if (e != hipSuccess) return e;
