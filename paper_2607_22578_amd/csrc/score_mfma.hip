@@ -162,9 +162,33 @@ struct Geo {
 // slices is a lower bound of the query's k-th best score.  An item starts
 // by raising the query's shared threshold to the best such bound over the
 // slices finished so far.
+// Long items with kWaveLists also publish, and raise their queries' thresholds,
+// while they run: after kLvlFirst tiles and whenever that number has doubled.
+// Slices that run at the same time then share one bound instead of each filling
+// a list of its own: 20M fp8 rows run as 14 slices of 3,720 tiles, all at once,
+// and queued 304 keys per query and slice before, 85 with it (68.9 -> 65.4 ms).
 constexpr int kLvl = 5;
+constexpr int kLvlFirst = 32;
 constexpr int kMWarmBytes = kMW * kMMQ * 4;   // per-wave warm-up minima (alias the queue)
 static_assert(kMWarmBytes <= kMMQ * kMQcap * 8, "warm-up minima fit in the queue");
+
+// Where the k-lists of an item live.
+// kLdsLists: in LDS, merged by a thread per query as soon as a queue is half
+//   full; for every k that fits beside the ring (18 or 19).
+// kTailLists: in the global partial buffer with the last kMTail entries in LDS,
+//   merged by a thread per query when a queue is full; up to k = kTailMax.
+// kWaveLists: in the global partial buffer alone, merged by a wave per query,
+//   whose cost is a read of the list whatever the number of keys, so the queues
+//   take the tail's place in LDS (24 keys).
+// The line between the last two, measured: 20M x 768 fp8, k = 100, 75.0 ms with
+// tails, 65.4-67.6 without; 500,009 x 400 fp8, k = 50, 885 us either way; 4M x
+// 1,024 bf16, k = 32, 79.0 ms either way; 333,333 x 1,000 bf16, k = 20, 460 us
+// with tails, 472 without (an end of item of 32 queries per wave).
+constexpr int kTailLists = 0, kLdsLists = 1, kWaveLists = 2;
+constexpr int kTailMax = 32;
+template <int LISTS>
+constexpr int kQcap = LISTS == kWaveLists ? 24 : kMQcap;   // queue slots per query
+static_assert(kQcap<kWaveLists> * 8 == kMQcap * 8 + kMTail * 8, "the same LDS as with tails");
 
 __host__ __device__ constexpr int mfma_lds_bytes(bool fp8, bool lds_lists, int k) {
   return (fp8 ? Geo<true>::ns * Geo<true>::stage + Geo<true>::nsc * kMSS * 4 +
@@ -313,7 +337,7 @@ __device__ __forceinline__ void mfma_step_il(f32x16m (&acc)[kMRB][NQB], const Fr
   }
 }
 
-template <bool FP8, bool LDS_LISTS>
+template <bool FP8, int LISTS>
 __device__ __forceinline__ MLds carve_mlds(unsigned char *p, int k) {
   using G = Geo<FP8>;
   MLds L;
@@ -322,15 +346,15 @@ __device__ __forceinline__ MLds carve_mlds(unsigned char *p, int k) {
   L.gtl = reinterpret_cast<uint32_t *>(p); p += G::ngt * kMGts * 4;
   L.queue = reinterpret_cast<uint64_t *>(p);
   L.warm = reinterpret_cast<float *>(p);   // (used before the queue in an epilogue)
-  p += kMMQ * kMQcap * 8;
+  p += kMMQ * kQcap<LISTS> * 8;
   L.lmin = reinterpret_cast<uint64_t *>(p); p += kMMQ * 8;
   L.qcount = reinterpret_cast<int32_t *>(p); p += kMMQ * 4;
   L.thr0 = reinterpret_cast<float *>(p); p += kMMQ * 4;
   L.thr = reinterpret_cast<float *>(p); p += kMMQ * 4;
   L.pub = reinterpret_cast<uint32_t *>(p); p += kMMQ * 4;
   L.flags = reinterpret_cast<int32_t *>(p); p += 16;
-  L.lists = LDS_LISTS ? reinterpret_cast<uint64_t *>(p) : nullptr;
-  L.tail = LDS_LISTS ? nullptr : reinterpret_cast<uint64_t *>(p);
+  L.lists = LISTS == kLdsLists ? reinterpret_cast<uint64_t *>(p) : nullptr;
+  L.tail = LISTS == kTailLists ? reinterpret_cast<uint64_t *>(p) : nullptr;
   (void)k;
   return L;
 }
@@ -380,6 +404,202 @@ __device__ __forceinline__ uint32_t level_bound(const uint32_t *lv, int S) {
   return b;
 }
 
+// An opaque copy of a lane value: values derived from it are recomputed
+// where they are used instead of being hoisted (and spilled) by the compiler.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// Merge the queued keys into the lists in the global partial buffer, a wave per
+// query (kWaveLists).  The list is sorted in descending order; L.lmin[q] holds its
+// length (what lies beyond it is not valid until the end of the item).  A list entry
+// moves down by the number of new keys above it, a new key goes to its rank
+// among the new keys plus the number of entries above it.  The list is read in
+// blocks of 64 entries from its end, up to the block whose first entry is above
+// every new key.  Entries and keys below the query's threshold cannot be in the
+// result and are dropped.
+//
+// One thread per query inserted its keys one after the other before, climbing
+// the list in windows of 8 dependent global reads, and the wave took as long as
+// its longest thread: 174,000 cycles per round of merges, 12.5 % of the main
+// pass over 20M fp8 rows, k = 100, with queues of 8.
+__device__ __forceinline__ uint64_t lane_key(uint64_t x, int f) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)x, f);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), f);
+  return ((uint64_t)hi << 32) | lo;
+}
+//
+// A wave has up to 32 queries (q = wave + 4 j); lane j holds the state of query
+// j, and the next query's keys and list block are on their way while one is
+// merged.  gt: shared thresholds of the item's queries.
+__device__ __forceinline__ void merge_lists(const MLds &L, const MfmaArgs &a, const MItem &it,
+                                            const uint32_t *gt) {
+  constexpr int QC = kQcap<kWaveLists>;
+  const int tid = opaque(threadIdx.x);   // (nothing below is worth a register outside)
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int k = a.k, mine = wv + kMW * lane;
+  const bool own = lane < kMMQ / kMW && mine < it.qvalid;
+  const float ninf = -__builtin_inff();
+  int cnt = own ? L.qcount[mine] : 0;
+  cnt = cnt < QC ? cnt : QC;
+  int fill = own ? (int)L.lmin[mine] : 0;
+  const float th0 = own ? L.thr[mine] : ninf;
+  uint32_t tho = th0 > ninf ? ord_score(th0) : 0u;
+  if (own && gt[mine] > tho) tho = gt[mine];
+  uint64_t todo = __builtin_amdgcn_ballot_w64(cnt > 0);
+  if (todo == 0ull) return;
+  float kth = ninf;   // lane j: score of query j's k-th key, if it has one now
+  uint64_t *const lists = a.part + ((int64_t)it.qbase * it.S + it.s) * k;
+  auto list = [&](int j) { return lists + (int64_t)(wv + kMW * j) * it.S * k; };
+  auto fetch = [&](int j, uint64_t &x, uint64_t &v) __attribute__((always_inline)) {
+    const int n = __builtin_amdgcn_readlane(cnt, j), f = __builtin_amdgcn_readlane(fill, j);
+    x = lane < n ? L.queue[(wv + kMW * j) * QC + lane] : 0ull;
+    const int i = ((f - 1) & ~63) + lane;
+    v = f > 0 && i < f ? list(j)[i] : 0ull;
+  };
+  int j = __builtin_ctzll(todo);
+  uint64_t x, v;
+  fetch(j, x, v);
+  for (;;) {
+    todo &= todo - 1ull;
+    const int jn = todo ? __builtin_ctzll(todo) : j;
+    const int n = __builtin_amdgcn_readlane(cnt, j), f0 = __builtin_amdgcn_readlane(fill, j);
+    const uint32_t drop = (uint32_t)__builtin_amdgcn_readlane((int)tho, j);
+    uint64_t xn = 0ull, vn = 0ull;
+    if (todo) fetch(jn, xn, vn);
+    uint64_t *l = list(j);
+    if ((uint32_t)(x >> 32) < drop) x = 0ull;
+    int pos = 0;   // the place of this lane's new key
+    for (int f = 0; f < n; ++f) pos += lane_key(x, f) > x ? 1 : 0;
+    uint64_t last = 0ull;   // the lane that holds the k-th key: that key
+    int live = 0;
+    for (int b = f0 > 0 ? (f0 - 1) & ~63 : -1; b >= 0; b -= 64) {
+      const int i = b + lane;
+      if (b != ((f0 - 1) & ~63)) v = l[i];
+      if ((uint32_t)(v >> 32) < drop) v = 0ull;
+      int shift = 0;
+      for (int f = 0; f < n; ++f) {
+        const uint64_t y = lane_key(x, f);
+        const int above = __builtin_popcountll(__builtin_amdgcn_ballot_w64(v > y));
+        pos += lane == f ? above : 0;
+        shift += y > v ? 1 : 0;
+      }
+      live += __builtin_popcountll(__builtin_amdgcn_ballot_w64(v != 0ull));
+      if (v != 0ull) {
+        const int p = i + shift;
+        if (shift > 0 && p < k) l[p] = v;
+        if (p == k - 1) last = v;
+      }
+      if (__builtin_amdgcn_readfirstlane(v != 0ull && shift == 0 ? 1 : 0)) {
+        pos += b;   // the entries of the earlier blocks are above every new key
+        live += b;
+        break;
+      }
+    }
+    if (x != 0ull) {
+      if (pos < k) l[pos] = x;
+      if (pos == k - 1) last = x;
+    }
+    live += __builtin_popcountll(__builtin_amdgcn_ballot_w64(x != 0ull));
+    const uint64_t has = __builtin_amdgcn_ballot_w64(last != 0ull);   // (at most one lane)
+    const float lk = has ? unord_score((uint32_t)(lane_key(last, __builtin_ctzll(has)) >> 32)) : ninf;
+    if (lane == j) {
+      fill = live < k ? live : k;
+      kth = lk;
+    }
+    if (!todo) break;
+    j = jn;
+    x = xn;
+    v = vn;
+  }
+  if (cnt > 0) {
+    L.qcount[mine] = 0;
+    L.lmin[mine] = (uint64_t)fill;
+    if (kth > th0) {
+      L.thr[mine] = kth;
+      publish_thr(L, a, it, mine, kth);
+    }
+  }
+}
+
+// The same, outside the tile epilogue.  Lists that are all empty (short
+// slices, whose only merge is that at their end) take no list reads, and half a
+// wave per query ranks its keys by counting.
+__device__ __forceinline__ void merge_any(const MLds &L, const MfmaArgs &a, const MItem &it,
+                                          const uint32_t *gt) {
+  constexpr int QC = kQcap<kWaveLists>;
+  static_assert(QC <= 32 && QC % 8 == 0, "a key per lane of half a wave, read by eights");
+  const int tid = opaque(threadIdx.x), lane = tid & 63, wv = tid >> 6, e = lane & 31;
+  const int mine = wv + kMW * e;
+  if (__builtin_amdgcn_ballot_w64(mine < it.qvalid && L.lmin[mine] != 0ull)) {
+    merge_lists(L, a, it, gt);
+    return;
+  }
+  for (int j = lane >> 5; j < kMMQ / kMW; j += 2) {
+    const int q = wv + kMW * j;
+    const float th = L.thr[q];
+    uint32_t drop = gt[q];
+    uint64_t x = e < QC ? L.queue[q * QC + e] : 0ull;
+    int n = q < it.qvalid ? L.qcount[q] : 0;
+    n = n < QC ? n : QC;
+    const uint32_t to = th > -__builtin_inff() ? ord_score(th) : 0u;
+    drop = to > drop ? to : drop;
+    if (e >= n || (uint32_t)(x >> 32) < drop) x = 0ull;
+    int pos = 0;
+    for (int f = 0; __builtin_amdgcn_ballot_w64(f < n); f += 8) {
+      uint64_t y[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) y[u] = L.queue[q * QC + f + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) pos += f + u < n && y[u] > x ? 1 : 0;
+    }
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(x != 0ull);
+    const int live = __builtin_popcount((uint32_t)(lane < 32 ? mask : mask >> 32));
+    if (x != 0ull && pos < a.k) {
+      a.part[((int64_t)(it.qbase + q) * it.S + it.s) * a.k + pos] = x;
+      const float sc = unord_score((uint32_t)(x >> 32));
+      if (pos == a.k - 1 && sc > th) {
+        L.thr[q] = sc;
+        publish_thr(L, a, it, q, sc);
+      }
+    }
+    if (e == 0 && n > 0) {
+      L.lmin[q] = (uint64_t)(live < a.k ? live : a.k);
+      L.qcount[q] = 0;
+    }
+  }
+}
+
+// Order statistics of the wave's lists so far (global lists): eight queries at
+// a time, a lane per query and level.
+__device__ __forceinline__ void publish_levels_wave(const MLds &L, const MfmaArgs &a,
+                                                    const MItem &it) {
+  const int tid = opaque(threadIdx.x), lane = tid & 63, wv = tid >> 6, l = lane & 7;
+  const int p = l < kLvl ? ((a.k + (1 << l) - 1) >> l) - 1 : a.k;   // ceil(k / 2^l) - 1
+#pragma unroll
+  for (int j0 = 0; j0 < kMMQ / kMW; j0 += 8) {
+    const int j = j0 + (lane >> 3);
+    const int q = wv + kMW * j;
+    if (q < it.qvalid && p < (int)L.lmin[q])
+      __hip_atomic_store(
+          a.lvl + (int64_t)(it.qbase + q) * kLvl * it.S + l * it.S + it.s,
+          (uint32_t)(a.part[((int64_t)(it.qbase + q) * it.S + it.s) * a.k + p] >> 32),
+          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Raise query t's threshold to the bound of the order statistics published so
+// far by all its slices.
+__device__ __forceinline__ void raise_by_levels(const MLds &L, const MfmaArgs &a, const MItem &it,
+                                                int t) {
+  const uint32_t b = level_bound(a.lvl + (int64_t)(it.qbase + t) * kLvl * it.S, (int)it.S);
+  if (b) {
+    L.thr[t] = fmaxf(L.thr[t], unord_score(b));
+    publish_thr(L, a, it, t, L.thr[t]);
+  }
+}
+
 // Keep the accumulators in AGPRs and make the compiler forget any VGPR copy
 // of them: the epilogue then reads each element where it is used instead of
 // holding all 256 in VGPRs across its loops.
@@ -389,13 +609,6 @@ __device__ __forceinline__ void pin_acc(f32x16m (&acc)[kMRB][NQB]) {
   for (int rb = 0; rb < kMRB; ++rb)
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) asm volatile("" : "+a"(acc[rb][qb]));
-}
-
-// An opaque copy of a lane value: values derived from it are recomputed
-// where they are used instead of being hoisted (and spilled) by the compiler.
-__device__ __forceinline__ int opaque(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 
 // Turns the tile's accumulators into scores in place, once per tile: the fp8
@@ -534,7 +747,7 @@ __device__ __forceinline__ void mtile_lane_maxima(const MfmaArgs &a, const MItem
 
 // Top-k epilogue of one tile.  row0 = corpus row of the tile's first row;
 // ssc = row scales of the tile (fp8).
-template <bool FP8, bool LDS_LISTS, int NQB>
+template <bool FP8, int LISTS, int NQB>
 __device__ __forceinline__ void mtile_epilogue(const MLds &L, const MfmaArgs &a, const MItem &it,
                                                f32x16m (&acc)[kMRB][NQB],
                                                float (&thr_r)[kMQB], int &epoch, int row0,
@@ -621,9 +834,9 @@ __device__ __forceinline__ void mtile_epilogue(const MLds &L, const MfmaArgs &a,
   // threads of the queries merge, the thresholds rise, and the candidates
   // left over are examined again.  A queue is due when half full if the
   // lists are in LDS, and only when full if they are in global memory,
-  // where a merge round (two barriers and climbs through global memory)
-  // costs more than the candidates a later threshold rise would save.
-  constexpr int qdue = LDS_LISTS ? kMQcap / 2 : kMQcap;
+  // where a merge round costs more than the candidates a later threshold rise
+  // would save.
+  constexpr int QC = kQcap<LISTS>, qdue = LISTS == kLdsLists ? QC / 2 : QC;
   for (;;) {
     bool ovf = false, full = false;
     pin_acc(acc);
@@ -652,7 +865,7 @@ __device__ __forceinline__ void mtile_epilogue(const MLds &L, const MfmaArgs &a,
         int slot = 0;
         if (cand) slot = atomicAdd(&L.qcount[ql], __builtin_popcount(cand));
         while (cand) {
-          if (slot >= kMQcap) {
+          if (slot >= QC) {
             fail |= (uint64_t)cand << (16 * rb);
             ovf = true;
             break;
@@ -673,7 +886,7 @@ __device__ __forceinline__ void mtile_epilogue(const MLds &L, const MfmaArgs &a,
           const uint32_t w2a = (w4[0] & ~m2) | (w4[1] & m2), w2b = (w4[2] & ~m2) | (w4[3] & m2);
           const float sc = __uint_as_float((w2a & ~m3) | (w2b & m3));
           full |= slot + 1 >= qdue;
-          L.queue[ql * kMQcap + slot] = make_key(sc, (uint32_t)(rowb + 8 * (jx >> 2) + (jx & 3)));
+          L.queue[ql * QC + slot] = make_key(sc, (uint32_t)(rowb + 8 * (jx >> 2) + (jx & 3)));
           ++slot;
         }
       }
@@ -687,7 +900,11 @@ __device__ __forceinline__ void mtile_epilogue(const MLds &L, const MfmaArgs &a,
       ++epoch;
       break;
     }
-    if (tid < it.qvalid) merge_queue<LDS_LISTS>(L, a, it, tid);
+    if constexpr (LISTS == kWaveLists) {
+      merge_lists(L, a, it, gt);
+    } else {
+      if (tid < it.qvalid) merge_queue<LISTS == kLdsLists>(L, a, it, tid);
+    }
     bar_lds();
 #pragma unroll
     for (int qb = 0; qb < kMQB; ++qb) thr_r[qb] = fmaxf(L.thr[qb * 32 + c], g_r[qb]);
@@ -701,7 +918,7 @@ __device__ __forceinline__ void mtile_epilogue(const MLds &L, const MfmaArgs &a,
 // steps and the epilogue skip the blocks past the item's queries (few
 // distinct queries).  The copies are those of a full
 // tile (the query rows past the item's queries read as zeros).
-template <bool FP8, bool LDS_LISTS, bool SEED, int NQB>
+template <bool FP8, int LISTS, bool SEED, int NQB>
 __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const Split &sp,
                                          int64_t nu, int w, int &epoch) {
   using G = Geo<FP8>;
@@ -754,9 +971,9 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
             L.pub[tid] = b;
           }
         }
-        if (LDS_LISTS) {
+        if (LISTS == kLdsLists) {
           for (int j = 0; j < a.k; ++j) L.lists[tid * a.k + j] = 0ull;
-        } else {
+        } else if (LISTS == kTailLists) {
           uint64_t *l = a.part + ((int64_t)(it.qbase + tid) * it.S + it.s) * a.k;
           for (int j = 0; j < a.k - kMTail; ++j) l[j] = 0ull;
           for (int j = 0; j < kMTail; ++j) L.tail[tid * kMTail + j] = 0ull;
@@ -974,6 +1191,8 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
     // is peeled so that the previous tile's accumulators are dead here.  The
     // last stage of a tile leaves the next fragments in LDS: the epilogue runs
     // with only the accumulators live, and f0 is refilled after it.)
+    const bool later = sp.qtiles * sp.S > a.grid;   // there are items that start later
+    int due = it.S > 1 ? kLvlFirst : 0;   // tiles done at the next publication
     for (int tl = 0; tl < ntl; ++tl) {
       if (nch > 1) {
         stage(std::true_type{}, std::true_type{});
@@ -986,9 +1205,27 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
         mtile_lane_maxima<FP8>(a, it, acc, (t0 + tl) * kMNC,
                                FP8 ? L.sscale + e_sc * kMSS : nullptr, tl);
       else
-        mtile_epilogue<FP8, LDS_LISTS>(L, a, it, acc, thr_r, epoch, (t0 + tl) * kMNC,
+        mtile_epilogue<FP8, LISTS>(L, a, it, acc, thr_r, epoch, (t0 + tl) * kMNC,
                                        FP8 ? L.sscale + e_sc * kMSS : nullptr,
                                        L.gtl + e_gt * kMGts, tl == 0);
+      if constexpr (!SEED && LISTS == kWaveLists) {
+        // merge what is still queued and publish the lists' order statistics;
+        // before the item's end, take what all slices have published
+        const bool end = tl + 1 == ntl;
+        if (end || tl + 1 == due) {
+          due *= 2;
+          bar_lds();
+          merge_any(L, a, it, L.gtl + e_gt * kMGts);
+          if (later || !end) publish_levels_wave(L, a, it);
+          bar_lds();
+          if (!end) {
+            if (tid < it.qvalid) raise_by_levels(L, a, it, tid);
+            bar_lds();
+#pragma unroll
+            for (int qb = 0; qb < kMQB; ++qb) thr_r[qb] = fmaxf(thr_r[qb], L.thr[qb * 32 + c]);
+          }
+        }
+      }
       if constexpr (FP8) e_sc = e_sc + 1 == G::nsc ? 0 : e_sc + 1;
       e_gt = e_gt + 1 == G::ngt ? 0 : e_gt + 1;
       read_frags<FP8>(f0, L.ring + r_slot * G::stage, wv, c, h, 0);
@@ -1002,10 +1239,10 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
       }
     }
     // merge what is still queued, then flush the LDS lists of this item
-    if constexpr (!SEED) {
+    if constexpr (!SEED && LISTS != kWaveLists) {
       bar_lds();
       if (tid < it.qvalid) {
-        merge_queue<LDS_LISTS>(L, a, it, tid);
+        merge_queue<LISTS == kLdsLists>(L, a, it, tid);
         // this slice's order statistics for the items that start later
         const uint64_t mn = L.lmin[tid];
         const int fill = (mn >> 32) ? a.k : (int)mn;
@@ -1015,7 +1252,7 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
           const int p = opaque(((a.k + (1 << l) - 1) >> l) - 1);   // ceil(k / 2^l) - 1
           if (p < fill) {
             uint64_t key;
-            if (LDS_LISTS)
+            if (LISTS == kLdsLists)
               key = L.lists[tid * a.k + p];
             else if (p >= a.k - kMTail)
               key = L.tail[tid * kMTail + p - (a.k - kMTail)];
@@ -1027,7 +1264,7 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
         }
       }
     }
-    if (LDS_LISTS && !SEED) {
+    if (LISTS == kLdsLists && !SEED) {
       bar_lds();
       const int tot = it.qvalid * a.k;
       for (int t = tid; t < tot; t += kMT) {
@@ -1035,7 +1272,15 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
         a.part[((int64_t)(it.qbase + q) * it.S + it.s) * a.k + j] = L.lists[t];
       }
     }
-    if (!LDS_LISTS && !SEED) {
+    if constexpr (!SEED && LISTS == kWaveLists) {   // empty slots
+      const int mine = wv + kMW * lane;
+      const int fill = lane < kMMQ / kMW && mine < it.qvalid ? (int)L.lmin[mine] : a.k;
+      for (int j = 0; j < kMMQ / kMW && wv + kMW * j < it.qvalid; ++j) {
+        uint64_t *l = a.part + ((int64_t)(it.qbase + wv + kMW * j) * it.S + it.s) * a.k;
+        for (int i = __builtin_amdgcn_readlane(fill, j) + lane; i < a.k; i += 64) l[i] = 0ull;
+      }
+    }
+    if (LISTS == kTailLists && !SEED) {
       bar_lds();
       const int tot = it.qvalid * kMTail;
       for (int t = tid; t < tot; t += kMT) {
@@ -1048,10 +1293,10 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
   }
 }
 
-template <bool FP8, bool LDS_LISTS, bool SEED>
+template <bool FP8, int LISTS, bool SEED>
 __global__ __launch_bounds__(kMT, 1) void score_mfma_dma(MfmaArgs a) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const MLds L = carve_mlds<FP8, LDS_LISTS>(smem, a.k);
+  const MLds L = carve_mlds<FP8, LISTS>(smem, a.k);
   const int64_t nu = read_nu(a.n_unique, a.n_unique_dev, a.cap);
   int64_t smax = kMSplitMaxSK / a.k;
   const Split sp = make_split(nu, a.N, kMMQ, kMNC, a.grid, smax < 1 ? 1 : smax);
@@ -1066,13 +1311,13 @@ __global__ __launch_bounds__(kMT, 1) void score_mfma_dma(MfmaArgs a) {
     // skips its empty query blocks.
     const int64_t qv = sp.qtiles > 1 ? kMMQ : nu;
     if (qv > 96)
-      run_item<FP8, LDS_LISTS, SEED, 4>(a, L, sp, nu, w, epoch);
+      run_item<FP8, LISTS, SEED, 4>(a, L, sp, nu, w, epoch);
     else if (qv > 64)
-      run_item<FP8, LDS_LISTS, SEED, 3>(a, L, sp, nu, w, epoch);
+      run_item<FP8, LISTS, SEED, 3>(a, L, sp, nu, w, epoch);
     else if (qv > 32)
-      run_item<FP8, LDS_LISTS, SEED, 2>(a, L, sp, nu, w, epoch);
+      run_item<FP8, LISTS, SEED, 2>(a, L, sp, nu, w, epoch);
     else
-      run_item<FP8, LDS_LISTS, SEED, 1>(a, L, sp, nu, w, epoch);
+      run_item<FP8, LISTS, SEED, 1>(a, L, sp, nu, w, epoch);
   }
 }
 
@@ -1407,12 +1652,17 @@ hipError_t launch_score_mfma(const void *q, const void *corpus, const float *sca
   const int lds = mfma_lds_bytes(fp8, ll, k);
   const int lds_seed = mfma_lds_bytes(fp8, false, k);
   auto run = [&](bool seed) {
-    if (seed) return fp8 ? launch_mfma(score_mfma_dma<true, false, true>, a.grid, lds_seed, a, st)
-                         : launch_mfma(score_mfma_dma<false, false, true>, a.grid, lds_seed, a, st);
-    if (fp8) return ll ? launch_mfma(score_mfma_dma<true, true, false>, a.grid, lds, a, st)
-                       : launch_mfma(score_mfma_dma<true, false, false>, a.grid, lds, a, st);
-    return ll ? launch_mfma(score_mfma_dma<false, true, false>, a.grid, lds, a, st)
-              : launch_mfma(score_mfma_dma<false, false, false>, a.grid, lds, a, st);
+    if (seed)
+      return fp8 ? launch_mfma(score_mfma_dma<true, kTailLists, true>, a.grid, lds_seed, a, st)
+                 : launch_mfma(score_mfma_dma<false, kTailLists, true>, a.grid, lds_seed, a, st);
+    if (ll)
+      return fp8 ? launch_mfma(score_mfma_dma<true, kLdsLists, false>, a.grid, lds, a, st)
+                 : launch_mfma(score_mfma_dma<false, kLdsLists, false>, a.grid, lds, a, st);
+    if (k > kTailMax)
+      return fp8 ? launch_mfma(score_mfma_dma<true, kWaveLists, false>, a.grid, lds, a, st)
+                 : launch_mfma(score_mfma_dma<false, kWaveLists, false>, a.grid, lds, a, st);
+    return fp8 ? launch_mfma(score_mfma_dma<true, kTailLists, false>, a.grid, lds, a, st)
+               : launch_mfma(score_mfma_dma<false, kTailLists, false>, a.grid, lds, a, st);
   };
   // Seed pass: score the first T tiles of every sampled slice (all slices, or
   // one in seed_stride(S)) and keep only lane maxima; their k-th largest per
