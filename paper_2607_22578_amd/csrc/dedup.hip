@@ -264,7 +264,7 @@ constexpr int kRadixGridMax = 256;    // workgroups of the persistent sort
 constexpr int kBarGroups = 16;        // arrival counters of the grid barrier
 constexpr int kCtlStride = 32;        // 32-bit words between counters (128 B)
 // control words: [0] value-block ticket of the groups launch; [kCtlFull] set
-// when the hash path has given up (a bucket is full); [kCtlWide] the first keys
+// when the hash path has given up (a bucket is full, or a search too long); [kCtlWide] the first keys
 // lie R or more apart; barrier
 // arrival counter j at (1 + j) * kCtlStride; the barrier's release counter at
 // (1 + kBarGroups) * kCtlStride
@@ -304,8 +304,15 @@ struct RadixWs {
 // signatures are hash values) fill a bucket to at most 256 on average, and
 // never to kBucketCap.  Keys that do are left to the sort.  Up to 2^20
 // requests: the table and the buckets take 90 bytes per request or more.
+//
+// A key's search in the table ends after kProbeMax slots.  In a table that is at
+// most half full the longest search is about ln(R) / 0.19 slots (72 for 2^20 keys),
+// but keys whose products with the hash's multiplier share their top bits (an
+// arithmetic progression of a suitable step does) would search all R: such keys are
+// left to the sort as well.
 constexpr int kHashRMax = 1 << 20;
 constexpr int kBucketCap = 1024;
+constexpr int kProbeMax = 256;
 __host__ __device__ __forceinline__ int hash_bits(int64_t R) {   // 2 R <= 2^bits < 4 R
   int b = 13;
   while (((int64_t)1 << b) < 2 * R) ++b;
@@ -533,8 +540,7 @@ constexpr int kDenseBlk = 1024;                        // values per value block
 constexpr int kDensePer = kDenseBlk / kRadixThreads;   // values per thread
 constexpr int kAggRound = 1024, kAggSlots = 2048;
 
-// Slot search of one key in the table: the slot that holds it, claimed if need
-// be (fresh: by this call).  There are more slots than keys.
+// First slot to search for a mapped key in a table of 2^bits slots.
 __device__ __forceinline__ uint32_t hash_of(uint64_t m, int bits) {
   return (uint32_t)((m * 0x9E3779B97F4A7C15ull) >> (64 - bits));
 }
@@ -545,7 +551,8 @@ __device__ __forceinline__ uint32_t hash_of(uint64_t m, int bits) {
 // probes are in flight together), adds the round's first request and count to
 // its slot and, if the key is new, appends it to its bucket.  idxB gets every
 // request's slot.  Bound by the latency of a few dependent device-scope
-// atomics per key.
+// atomics per key.  Once any workgroup has given up (kCtlFull) the others do no
+// more than they have begun.
 __device__ void hash_insert(int R, const Range &rg, const RadixWs &ws, unsigned char *lds) {
   constexpr int per = kAggRound / kRadixThreads;
   unsigned long long *lk = (unsigned long long *)lds;   // mapped key (0: empty)
@@ -556,6 +563,12 @@ __device__ void hash_insert(int R, const Range &rg, const RadixWs &ws, unsigned 
   const uint32_t hmask = (1u << hbits) - 1u;
   constexpr int lbits = 11;
   static_assert((1 << lbits) == kAggSlots, "LDS table");
+  auto full = [&]() {
+    return __hip_atomic_load(&ws.ctl[kCtlFull], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+  };
+  auto give_up = [&]() {
+    __hip_atomic_store(&ws.ctl[kCtlFull], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   for (int64_t round = blockIdx.x; round * kAggRound < R; round += gridDim.x) {
     const int64_t base = round * kAggRound;
     for (int j = tid; j < kAggSlots; j += kRadixThreads) {
@@ -607,7 +620,12 @@ __device__ void hash_insert(int R, const Range &rg, const RadixWs &ws, unsigned 
     }
 #pragma unroll
     for (int e = 0; e < per; ++e) {
-      while (prev[e] != 0ull && prev[e] != m[e]) {   // (R keys, 2 R slots or more)
+      for (int left = kProbeMax; prev[e] != 0ull && prev[e] != m[e]; --left) {
+        if (left == 0 || ((left & 15) == 8 && full())) {
+          give_up();
+          own[e] = false;   // (nobody reads what would follow)
+          break;
+        }
         gs[e] = (gs[e] + 1) & hmask;
         prev[e] = atomicCAS(&ws.hk[gs[e]], 0ull, m[e]);
       }
@@ -623,7 +641,7 @@ __device__ void hash_insert(int R, const Range &rg, const RadixWs &ws, unsigned 
         ws.bkey[(int64_t)b * kBucketCap + at] = key;
         ws.bslot[(int64_t)b * kBucketCap + at] = (int32_t)slot;
       } else {
-        __hip_atomic_store(&ws.ctl[kCtlFull], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        give_up();
       }
     };
 #pragma unroll

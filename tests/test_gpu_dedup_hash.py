@@ -94,3 +94,15 @@ def test_one_workgroup_ranking(R, kind):
         keys[:2] = I64.min, I64.max
     _check(keys)
     _check(keys[rng.integers(0, R, size=R)], runs=1)
+
+
+@pytest.mark.parametrize("R", [3_000, 20_000, 200_000, 1 << 20])
+def test_keys_whose_hashes_share_their_top_bits(R):
+    # mapped keys j / 0x9E3779B97F4A7C15 (mod 2^64): the multiplicative hash of the
+    # j-th is j, so every search begins at the first slot of the table.  Searches
+    # are bounded (the sort takes over); without that R keys take R^2 / 2 steps
+    note(f"dedup colliding hashes R={R}")
+    inv = pow(0x9E3779B97F4A7C15, -1, 1 << 64)
+    j = np.random.default_rng(R).permutation(R).astype(np.uint64) + np.uint64(1)
+    mapped = j * np.uint64(inv)      # (wraps mod 2^64)
+    _check((mapped ^ np.uint64(1 << 63)).view(np.int64))
