@@ -15,7 +15,7 @@
 //                    and maps every request to its group through the table;
 //   larger R       : the key range is found on the device; keys that take at
 //                    most R values are grouped by direct addressing over the
-//                    range; keys spread over a wide range (signatures) by a
+//                    range; keys spread evenly over a wide range (signatures) by a
 //                    hash table in the workspace, their distinct values
 //                    ordered bucket by bucket of the range; others by an LSD
 //                    radix sort (8-bit digits over key - min, so only the bits
@@ -264,20 +264,20 @@ constexpr int kRadixGridMax = 256;    // workgroups of the persistent sort
 constexpr int kBarGroups = 16;        // arrival counters of the grid barrier
 constexpr int kCtlStride = 32;        // 32-bit words between counters (128 B)
 // control words: [0] value-block ticket of the groups launch; [kCtlFull] set
-// when the hash path has given up (a bucket is full, or a search too long); [kCtlWide] the first keys
-// lie R or more apart; barrier
-// arrival counter j at (1 + j) * kCtlStride; the barrier's release counter at
+// when the hash path has given up (a bucket is full, or a search too long);
+// [kCtlSpread] the sampled keys suit the hash path; barrier arrival counter j at (1 + j) * kCtlStride; the barrier's release counter at
 // (1 + kBarGroups) * kCtlStride
 constexpr int kCtlWords = (2 + kBarGroups) * kCtlStride;
-constexpr int kCtlFull = 1, kCtlWide = 2;
-constexpr int kWideKeys = 1024;
+constexpr int kCtlFull = 1, kCtlSpread = 2;
+constexpr int kSampleKeys = 1024;   // the first keys of the window
 
 struct RadixWs {
   uint64_t *keyA, *keyB;
   int32_t *idxA, *idxB;
   uint64_t *pmin, *pmax;   // per-prep-workgroup min/max of mapped keys
   uint64_t *range;         // [0] = global min, [1] = radix pass count,
-                           // [2] = key values of the dense path (0: radix)
+                           // [2] = key values of the dense path (0: others),
+                           // [3] = hash path, [4] = range of the sampled keys
   uint32_t *hist;          // kBins x nb, digit-major (scanned in place)
   uint32_t *dtot;          // kBins digit totals of a pass
   uint32_t *bheads;        // heads per tile (scanned in place)
@@ -319,6 +319,11 @@ __host__ __device__ __forceinline__ int hash_bits(int64_t R) {   // 2 R <= 2^bit
   return b;
 }
 __host__ __device__ __forceinline__ int bucket_bits(int hbits) { return hbits - 9; }
+// A key's bucket is (key - min) >> shift, with keys `span` apart.
+__device__ __forceinline__ int bucket_shift(uint64_t span, int hbits) {
+  const int bits = 64 - __clzll((long long)span), bb = bucket_bits(hbits);   // (span > 0)
+  return bits > bb ? bits - bb : 0;
+}
 
 // ------------------------------------------------ grid-wide helpers
 
@@ -378,6 +383,98 @@ __device__ uint32_t block_scan_inplace(uint32_t *a, int64_t n) {
 
 // ------------------------------------------------ prep and path choice
 
+// First slot to search for a mapped key in a table of 2^bits slots.
+__device__ __forceinline__ uint32_t hash_of(uint64_t m, int bits) {
+  return (uint32_t)((m * 0x9E3779B97F4A7C15ull) >> (64 - bits));
+}
+
+// Whether the keys suit the hash path, from a sample: the window's first 1,024.
+// They must lie R or more apart and no bucket may be expected to fill.  Clustered
+// keys (ids under a few tenants, dense ids and a sentinel) put most of the range's
+// keys in a few buckets: one counter then takes an atomic add for every key, 11 ns
+// each, and the sort still follows.  200,000 dense ids and one far key: 2,680 us,
+// the sort alone 404; a million ids under two tenants 5,452, 903.
+//
+// n distinct keys of the sample with p ordered pairs of them in one bucket: the
+// keys that share a random key's bucket are about D p / n^2 of D distinct ones,
+// and D is at most R n / 1024 (new keys get rarer).  Signatures have 512 at most
+// (twice R / buckets, half of the buckets used) with a deviation of 32; the limit
+// lies between that and the bucket's size.  A search of more than 128 slots here
+// (36 are usual for 1,024 keys in 2,048 slots) tells keys that the hash does not
+// spread.
+constexpr uint64_t kSpreadMax = 768;
+__device__ void sample_spread(const int64_t *__restrict__ keys, int R, const RadixWs &ws) {
+  constexpr int per = kSampleKeys / kRadixThreads, slots = 2 * kSampleKeys, W = kRadixThreads / 64;
+  constexpr int lbits = 11, kBucketsMax = 1 << 12;
+  static_assert(slots == 1 << lbits && kHashRMax == 1 << 20, "sample table, buckets of 2^20 keys");
+  __shared__ unsigned long long set[slots];
+  __shared__ uint32_t cnt[kBucketsMax];
+  __shared__ uint64_t smin[W], smax[W];
+  __shared__ uint32_t total, longer;   // distinct keys << 21 | pairs (< 2^20); a search too long
+  const int tid = threadIdx.x;
+  uint64_t m[per], mn = ~0ull, mx = 0ull;
+#pragma unroll
+  for (int e = 0; e < per; ++e) {
+    m[e] = map_key(keys[e * kRadixThreads + tid]);   // (R > kSmallMax)
+    mn = m[e] < mn ? m[e] : mn;
+    mx = m[e] > mx ? m[e] : mx;
+  }
+  for (int i = tid; i < slots; i += kRadixThreads) set[i] = 0ull;
+  for (int i = tid; i < 1 << bucket_bits(ws.hbits); i += kRadixThreads) cnt[i] = 0u;
+  if (tid == 0) total = longer = 0u;
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
+    mn = a < mn ? a : mn;
+    mx = c > mx ? c : mx;
+  }
+  if ((tid & 63) == 0) {
+    smin[tid >> 6] = mn;
+    smax[tid >> 6] = mx;
+  }
+  __syncthreads();
+  for (int w = 0; w < W; ++w) {
+    mn = smin[w] < mn ? smin[w] : mn;
+    mx = smax[w] > mx ? smax[w] : mx;
+  }
+  const uint64_t span = mx - mn;
+  if (span < (uint64_t)R) {
+    if (tid == 0) ws.ctl[kCtlSpread] = 0u;
+    return;
+  }
+  const int shift = bucket_shift(span, ws.hbits);
+  // (the four keys' first steps are in flight together; 0, the mark of an empty
+  // slot, is one key at most and is not counted)
+  uint32_t h[per], sum = 0u;
+  unsigned long long prev[per];
+#pragma unroll
+  for (int e = 0; e < per; ++e) {
+    h[e] = hash_of(m[e], lbits) & (slots - 1);
+    prev[e] = atomicCAS(&set[h[e]], 0ull, m[e]);
+  }
+#pragma unroll
+  for (int e = 0; e < per; ++e) {
+    int left = 128;
+    while (prev[e] != 0ull && prev[e] != m[e] && --left > 0) {
+      h[e] = (h[e] + 1) & (slots - 1);
+      prev[e] = atomicCAS(&set[h[e]], 0ull, m[e]);
+    }
+    if (left == 0) longer = 1u;
+  }
+#pragma unroll
+  for (int e = 0; e < per; ++e)
+    if (prev[e] == 0ull && m[e] != 0ull)
+      sum += (1u << 21) + 2u * atomicAdd(&cnt[(uint32_t)((m[e] - mn) >> shift)], 1u);
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if ((tid & 63) == 0) atomicAdd(&total, sum);
+  __syncthreads();
+  if (tid == 0) {
+    const uint64_t n = total >> 21, pairs = total & ((1u << 21) - 1u);
+    const bool fit = longer == 0u && (uint64_t)R * pairs <= kSpreadMax * kSampleKeys * n;
+    ws.ctl[kCtlSpread] = fit ? 1u : 0u;
+    ws.range[4] = span;
+  }
+}
+
 // Workgroup b of P: chunks of kPrepChunk requests b, b + P, ... -> mapped
 // keys (keyA), request numbers (idxA) and the min/max over them; the dense
 // tables for up to R values, the value-block words and the control words to
@@ -386,7 +483,11 @@ constexpr int kPrepChunk = 4 * kRadixThreads;
 __global__ __launch_bounds__(kRadixThreads) void dedup_prep_kernel(
     const int64_t *__restrict__ keys, int R, RadixWs ws) {
   __shared__ uint64_t smin[kRadixThreads / 64], smax[kRadixThreads / 64];
-  const int tid = threadIdx.x, P = gridDim.x;
+  const int tid = threadIdx.x, P = gridDim.x - (ws.hbits ? 1 : 0);
+  if ((int)blockIdx.x == P) {
+    sample_spread(keys, R, ws);
+    return;
+  }
   uint64_t mn = ~0ull, mx = 0ull;
   for (int64_t c = blockIdx.x; c * kPrepChunk < R; c += P) {
 #pragma unroll
@@ -431,17 +532,18 @@ __global__ __launch_bounds__(kRadixThreads) void dedup_prep_kernel(
   for (int64_t i = gt; i < nvb; i += gs) ws.flags[i] = 0ull;
   if (blockIdx.x == 0)
     for (int i = tid; i < kCtlWords; i += kRadixThreads)
-      if (i != kCtlWide) ws.ctl[i] = 0u;
+      if (i != kCtlSpread) ws.ctl[i] = 0u;
   // The hash path is taken only where the first 1,024 keys already lie R or
   // more apart, which every workgroup here can tell (so the dense path, whose
   // keys do not, pays nothing for it): each then clears its share of the table
-  // and the bucket counts.
+  // and the bucket counts.  The last workgroup decides from the same keys
+  // whether they suit the path.
   if (!ws.hbits) return;
   __shared__ int wide;
   mn = ~0ull;
   mx = 0ull;
 #pragma unroll
-  for (int e = 0; e < kWideKeys / kRadixThreads; ++e) {
+  for (int e = 0; e < kSampleKeys / kRadixThreads; ++e) {
     const uint64_t k = map_key(keys[e * kRadixThreads + tid]);   // (R > kSmallMax)
     mn = k < mn ? k : mn;
     mx = k > mx ? k : mx;
@@ -463,7 +565,6 @@ __global__ __launch_bounds__(kRadixThreads) void dedup_prep_kernel(
       mx = smax[w] > mx ? smax[w] : mx;
     }
     wide = mx - mn >= (uint64_t)R;
-    if (blockIdx.x == 0) ws.ctl[kCtlWide] = wide ? 1u : 0u;
   }
   __syncthreads();
   if (!wide) return;
@@ -485,13 +586,15 @@ struct Range {
 };
 
 // Global min/max over the P prep partials and the path: dense when the keys
-// take at most R values (max - min < R), else by hashing where prep has cleared
-// the table, else radix with one pass per 8 bits of max - min.  Computed by
+// take at most R values (max - min < R), else by hashing where the sampled keys
+// suit it (prep has then cleared the table), else radix with one pass per 8 bits of max - min.  Computed by
 // every workgroup that calls it.
 __device__ Range range_of(int R, int P, const RadixWs &ws) {
   __shared__ uint64_t smin[kRadixThreads / 64], smax[kRadixThreads / 64];
   __shared__ Range res;
   const int tid = threadIdx.x;
+  const bool spread = ws.hbits && ws.ctl[kCtlSpread] != 0u;
+  const uint64_t sample = ws.range[4];   // (written where spread)
   uint64_t mn = ~0ull, mx = 0ull;
   for (int i = tid; i < P; i += kRadixThreads) {
     mn = ws.pmin[i] < mn ? ws.pmin[i] : mn;
@@ -518,9 +621,9 @@ __device__ Range range_of(int R, int P, const RadixWs &ws) {
     res.mn = mn;
     res.npass = dense ? 0ull : (uint64_t)((bits + kRadixBits - 1) / kRadixBits);
     res.nv = dense ? span + 1 : 0ull;
-    res.hash = !dense && ws.hbits && ws.ctl[kCtlWide] ? 1 : 0;
-    const int bb = bucket_bits(ws.hbits);
-    res.hash_shift = bits > bb ? bits - bb : 0;
+    // (a range of twice the sample's or more has keys that the sample did not see)
+    res.hash = !dense && spread && span >> 1 <= sample ? 1 : 0;
+    res.hash_shift = dense ? 0 : bucket_shift(span, ws.hbits);
   }
   __syncthreads();
   return res;
@@ -539,11 +642,6 @@ __device__ Range range_of(int R, int P, const RadixWs &ws) {
 constexpr int kDenseBlk = 1024;                        // values per value block
 constexpr int kDensePer = kDenseBlk / kRadixThreads;   // values per thread
 constexpr int kAggRound = 1024, kAggSlots = 2048;
-
-// First slot to search for a mapped key in a table of 2^bits slots.
-__device__ __forceinline__ uint32_t hash_of(uint64_t m, int bits) {
-  return (uint32_t)((m * 0x9E3779B97F4A7C15ull) >> (64 - bits));
-}
 
 // Hash path of the marking launch.  Rounds of kAggRound consecutive requests
 // are first combined per key in an LDS table; the thread that entered a key
@@ -1107,7 +1205,7 @@ size_t dedup_workspace_bytes(int64_t R) {
   s += 2 * align_up(sizeof(uint64_t) * R);
   s += 2 * align_up(sizeof(int32_t) * R);
   s += 2 * align_up(sizeof(uint64_t) * kPrepMax);
-  s += align_up(sizeof(uint64_t) * 4);
+  s += align_up(sizeof(uint64_t) * 5);
   s += align_up(sizeof(uint32_t) * kBins * nb);
   s += align_up(sizeof(uint32_t) * kBins);
   s += align_up(sizeof(uint32_t) * nb);
@@ -1162,7 +1260,7 @@ hipError_t launch_dedup(const int64_t *keys, int64_t R, int64_t *uk, int32_t *fi
   w.idxB = (int32_t *)p; p += align_up(sizeof(int32_t) * R);
   w.pmin = (uint64_t *)p; p += align_up(sizeof(uint64_t) * kPrepMax);
   w.pmax = (uint64_t *)p; p += align_up(sizeof(uint64_t) * kPrepMax);
-  w.range = (uint64_t *)p; p += align_up(sizeof(uint64_t) * 4);
+  w.range = (uint64_t *)p; p += align_up(sizeof(uint64_t) * 5);
   w.hist = (uint32_t *)p; p += align_up(sizeof(uint32_t) * kBins * nb);
   w.dtot = (uint32_t *)p; p += align_up(sizeof(uint32_t) * kBins);
   w.bheads = (uint32_t *)p; p += align_up(sizeof(uint32_t) * nb);
@@ -1185,7 +1283,7 @@ hipError_t launch_dedup(const int64_t *keys, int64_t R, int64_t *uk, int32_t *fi
   int Ri = (int)R;
   const int64_t chunks = (R + kPrepChunk - 1) / kPrepChunk;
   const int P = chunks < kPrepMax ? (int)chunks : kPrepMax;
-  hipLaunchKernelGGL(dedup_prep_kernel, dim3(P), dim3(kRadixThreads), 0, st, keys, Ri, w);
+  hipLaunchKernelGGL(dedup_prep_kernel, dim3(P + (w.hbits ? 1 : 0)), dim3(kRadixThreads), 0, st, keys, Ri, w);
   int64_t rounds = (R + kAggRound - 1) / kAggRound;
   if (rounds > 4096) rounds = 4096;
   hipLaunchKernelGGL(dense_mark_kernel, dim3((unsigned)rounds), dim3(kRadixThreads), 0, st, Ri,

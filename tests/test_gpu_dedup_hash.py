@@ -106,3 +106,52 @@ def test_keys_whose_hashes_share_their_top_bits(R):
     j = np.random.default_rng(R).permutation(R).astype(np.uint64) + np.uint64(1)
     mapped = j * np.uint64(inv)      # (wraps mod 2^64)
     _check((mapped ^ np.uint64(1 << 63)).view(np.int64))
+
+
+def _time(keys, runs=5):
+    """Shortest of a few hs_dedup calls, in ms, between events on the stream."""
+    import paper_2607_22578_amd as hs
+    dev, R = device(), keys.shape[0]
+    plan = hs.hs_merge_plan(R, 8, 1, 1, hs.HS_BF16, hs.HS_BF16)
+    ws = torch.empty(max(plan.workspace_bytes, 256), dtype=torch.uint8, device=dev)
+    out = [torch.empty(R, dtype=t, device=dev)
+           for t in (torch.int64, torch.int32, torch.int32, torch.int32)]
+    nu, kd, best = torch.zeros(1, dtype=torch.int64, device=dev), to_dev(keys), float("inf")
+    for _ in range(runs):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        hs.hs_dedup(plan, kd, *out, nu, None, ws)
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("R", [20_000, 200_000, 1_000_000])
+@pytest.mark.parametrize("kind", ["sentinel", "late sentinel", "2 tenants", "16 tenants",
+                                  "30% clustered"])
+def test_clustered_wide_keys_cost_no_more_than_the_sort(R, kind):
+    # keys with most of them in a few buckets of a wide range go to the sort without an
+    # attempt on the table.  The same keys with their first 1,024 alike are sorted at
+    # once: the measure, of which the attempt took 1.2 to 10 times
+    note(f"dedup {kind} R={R}")
+    rng = np.random.default_rng(R + len(kind))
+    if kind == "sentinel":
+        keys = rng.permutation(R)
+        keys[0] = I64.max
+    elif kind == "late sentinel":          # ids of 40 bits, and one key far above
+        keys = rng.integers(0, 1 << 40, size=R)
+        keys[R // 2] = I64.max
+    elif kind == "30% clustered":
+        keys = _uniform(rng, R)
+        near = rng.random(R) < 0.3
+        keys[near] = rng.permutation(R)[:near.sum()]
+    else:
+        T = int(kind.split()[0])
+        keys = rng.integers(0, 2 * R // T, size=R) + (rng.integers(0, T, size=R) << 32)
+    keys = keys.astype(np.int64)
+    _check(keys)
+    at_once = keys.copy()
+    at_once[:2_048] = np.r_[np.full(1_024, keys[2_100]), keys[:1_024]]   # (the same range)
+    t, sort = _time(keys), _time(at_once)
+    assert t < 1.2 * sort + 0.02, f"{t * 1e3:.0f} us, the sort alone {sort * 1e3:.0f} us"
