@@ -75,14 +75,20 @@ __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t v, uint32_t *w
 
 constexpr int kRankDirect = 512;     // distinct keys ranked over all of them up to here
 constexpr int kRankBuckets = 512;    // buckets of the key range above
+constexpr int kRankCrowded = 80;     // keys in a bucket that call for other buckets
 
 // One workgroup; RMAX requests at most, in a table of twice as many slots.
 // Bound by latency: a few barriers, and the ranking.  Ranking every distinct key
 // by counting all of them takes n^2 LDS reads: 1.2 us of the 9 us for 329
 // keys, but most of the time from about a thousand.  Above kRankDirect, the keys
 // are first put into kRankBuckets buckets of their range, and a key counts only
-// those of its bucket (with keys in few buckets, as many reads as before).
-// 3,000 requests, 960 distinct: 56 us by a bitonic sort of the requests.
+// those of its bucket.  3,000 requests, 960 distinct: 56 us by a bitonic sort of
+// the requests.
+// Keys that crowd the range's buckets (ids under a few tenants, dense ids and a
+// sentinel) get buckets between RMAX / 8 of their own number instead, taken evenly
+// from the table's order, which is that of the hash.  4,096 keys, all but one
+// dense: 46 us, 1,496 with the range's buckets; in 64 clusters: 47 us either way
+// (the line: uniform keys have 16 or less in a bucket).
 template <int RMAX>
 __global__ __launch_bounds__(kSmallThreads) void dedup_hash_kernel(
     const int64_t *__restrict__ keys, int R, int64_t *__restrict__ uk, int32_t *__restrict__ fi,
@@ -100,7 +106,7 @@ __global__ __launch_bounds__(kSmallThreads) void dedup_hash_kernel(
   __shared__ uint32_t bcnt[kRankBuckets], bat[kRankBuckets];
   __shared__ uint64_t smin[kSmallThreads / 64], smax[kSmallThreads / 64];
   __shared__ uint32_t wsum[kSmallThreads / 64 + 1];
-  __shared__ int32_t ncomp;
+  __shared__ int32_t ncomp, crowded;
   const int tid = threadIdx.x;
   for (int t = tid; t <= SLOTS; t += kSmallThreads) {
     hk[t] = 0ull;
@@ -108,7 +114,7 @@ __global__ __launch_bounds__(kSmallThreads) void dedup_hash_kernel(
     hcnt[t] = 0;
   }
   if (tid < kRankBuckets) bcnt[tid] = 0u;
-  if (tid == 0) ncomp = 0;
+  if (tid == 0) ncomp = crowded = 0;
   __syncthreads();
   int myslot[PER];
 #pragma unroll
@@ -202,7 +208,50 @@ __global__ __launch_bounds__(kSmallThreads) void dedup_hash_kernel(
         mat[e] = atomicAdd(&bcnt[mb[e]], 1u);
       }
     }
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      if (msl[e] >= 0 && mat[e] >= (uint32_t)kRankCrowded) crowded = 1;
     __syncthreads();
+    if (crowded) {
+      // the sampled keys, sorted by counting, T threads to each
+      constexpr int M = RMAX / 8, T = kSmallThreads / M;
+      static_assert(M <= kRankBuckets && M <= kRankDirect && M % (8 * T) == 0, "sampled keys");
+      const int u = tid / T, part = tid % T;
+      const uint64_t x = hk[order[u * n / M]];   // (n > kRankDirect: distinct)
+      if (part == 0) ck[u] = x;
+      if (tid < kRankBuckets) bcnt[tid] = 0u;
+      __syncthreads();
+      int r = 0;
+      for (int j = part * (M / T); j < (part + 1) * (M / T); j += 8) {
+        uint64_t y[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) y[t] = ck[j + t];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) r += y[t] < x ? 1 : 0;
+      }
+#pragma unroll
+      for (int o = 1; o < T; o <<= 1) r += __shfl_xor(r, o, 64);
+      __syncthreads();
+      if (part == 0) ck[r] = x;
+      __syncthreads();
+      // a key's bucket: the last of them that is not above it, or the first
+      int lo[PER];
+#pragma unroll
+      for (int e = 0; e < PER; ++e) lo[e] = 0;
+#pragma unroll 1
+      for (int half = M / 2; half > 0; half >>= 1) {
+#pragma unroll
+        for (int e = 0; e < PER; ++e)
+          if (msl[e] >= 0 && ck[lo[e] + half] <= hk[msl[e]]) lo[e] += half;
+      }
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        if (msl[e] < 0) continue;
+        mb[e] = (uint32_t)lo[e];
+        mat[e] = atomicAdd(&bcnt[lo[e]], 1u);
+      }
+      __syncthreads();
+    }
     uint32_t total;
     const uint32_t c = tid < kRankBuckets ? bcnt[tid] : 0u;
     const uint32_t incl = block_inclusive_scan<kSmallThreads>(c, wsum, total);

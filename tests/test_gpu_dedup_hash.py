@@ -155,3 +155,25 @@ def test_clustered_wide_keys_cost_no_more_than_the_sort(R, kind):
     at_once[:2_048] = np.r_[np.full(1_024, keys[2_100]), keys[:1_024]]   # (the same range)
     t, sort = _time(keys), _time(at_once)
     assert t < 1.2 * sort + 0.02, f"{t * 1e3:.0f} us, the sort alone {sort * 1e3:.0f} us"
+
+
+@pytest.mark.parametrize("R", [600, 1_500, 2_048, 2_049, 4_096])
+@pytest.mark.parametrize("kind", ["sentinel", "2 tenants", "64 tenants", "powers"])
+def test_one_workgroup_ranking_of_clustered_keys(R, kind):
+    # keys that lie in few buckets of their range are ranked in about the time of
+    # uniform ones (4 to 65 times it while a bucket's keys were all compared)
+    note(f"dedup {kind} R={R}")
+    rng = np.random.default_rng(R + len(kind))
+    keys = rng.permutation(R)
+    if kind == "sentinel":
+        keys[0] = I64.max
+    elif kind == "powers":                 # every scale from 1 to 2^62
+        keys = np.unique((2.0 ** rng.uniform(0, 62, 4 * R)).astype(np.int64))
+        keys = rng.permutation(keys)[:R]
+    else:
+        keys = keys + (rng.integers(0, int(kind.split()[0]), size=R) << 40)
+    keys = keys.astype(np.int64)
+    _check(keys)
+    _check(keys[rng.integers(0, keys.size, size=R)], runs=1)
+    t, uniform = _time(keys), _time(_uniform(rng, R))
+    assert t < 2 * uniform + 0.005, f"{t * 1e3:.1f} us, uniform keys {uniform * 1e3:.1f} us"
