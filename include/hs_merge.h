@@ -181,10 +181,11 @@ hs_status hs_score_topk(const hs_plan *plan, const void *q_unique, int64_t n_uni
  * array the library holds on each GPU (64 MiB per GPU, allocated with the
  * library's code object and kept until the process ends) instead of a
  * workspace argument.  No hipMalloc, hipFree or other allocation happens in
- * the call.  A plan whose score workspace (what hs_merge_plan reports for the
- * score step) exceeds 64 MiB is rejected with HS_ERR_WORKSPACE before
- * anything is enqueued; the 1M-row window (2,048 requests, d = 768, k = 10)
- * needs about 62 MiB.  Every call on one GPU uses that GPU's one array, which
+ * the call.  A plan whose score step needs more scratch than 64 MiB is rejected
+ * with HS_ERR_WORKSPACE before anything is enqueued; the 1M-row window (2,048
+ * requests, d = 768, k = 10, bf16) needs about 62 MiB.  (F32 plans do with a list
+ * of k entries per request, 8 bytes each, and run as fewer corpus slices where
+ * there is no room for more.)  Every call on one GPU uses that GPU's one array, which
  * keeps the previous call's contents (each call writes everything it reads
  * before reading it): calls that overlap in time on one GPU -- on different
  * streams, or from host threads without ordering -- race and give wrong

@@ -26,17 +26,18 @@ hipError_t launch_deliver(const float *ts, const int32_t *ti, int64_t rows, cons
                           int64_t R, int k, float *os, int32_t *oi, hipStream_t st);
 size_t noalloc_scratch_bytes();
 hipError_t noalloc_scratch(void **ptr);
-size_t score_workspace_bytes(int64_t cap, int64_t N, int64_t d, int k, int corpus_dtype);
+size_t score_workspace_bytes(int64_t cap, int64_t N, int64_t d, int k, int corpus_dtype,
+                             size_t limit);
 hipError_t launch_score_partial(const void *q, const void *corpus, const float *scale, int64_t N,
                                 int64_t d, int k, int64_t n_unique, const int64_t *nu_dev,
-                                int64_t cap, int corpus_dtype, bool tiled, void *part,
-                                hipStream_t st);
+                                int64_t cap, int corpus_dtype, bool tiled, size_t limit,
+                                void *part, hipStream_t st);
 size_t mfma_tiled_bytes(int64_t N, int64_t d, bool fp8);
 hipError_t launch_tile_corpus(const void *corpus, int64_t N, int64_t d, bool fp8, void *tiled,
                               hipStream_t st);
 hipError_t launch_topk_merge(const void *part, int64_t n_unique, const int64_t *nu_dev,
-                             int64_t cap, int64_t N, int k, int corpus_dtype, float *out_s,
-                             int32_t *out_i, hipStream_t st);
+                             int64_t cap, int64_t N, int64_t d, int k, int corpus_dtype,
+                             size_t limit, float *out_s, int32_t *out_i, hipStream_t st);
 struct CacheView;
 size_t cache_layout(int64_t C, int k, void *base, CacheView *v);
 hipError_t launch_cache_reset(void *cache, int64_t C, int k, hipStream_t st);
@@ -67,6 +68,7 @@ struct hs_plan {
   int64_t cap;          // max distinct keys
   size_t ws_dedup;      // bytes used by hs_dedup (offset 0)
   size_t ws_score;      // bytes used by the score phases (offset 0)
+  size_t ws_noalloc;    // the same laid out for the library's own scratch
   size_t ws_prio;       // bytes used by hs_priority (offset 0)
   size_t ws_total;
 };
@@ -181,7 +183,9 @@ hs_status hs_merge_plan(const hs_merge_desc *desc, hs_plan **plan, size_t *works
   p->d.workflow_offsets = nullptr;
   p->cap = d.max_unique > 0 ? d.max_unique : d.n_requests;
   p->ws_dedup = hs::dedup_workspace_bytes(d.n_requests);
-  p->ws_score = hs::score_workspace_bytes(p->cap, d.n_corpus, d.dim, d.k, d.corpus_dtype);
+  p->ws_score = hs::score_workspace_bytes(p->cap, d.n_corpus, d.dim, d.k, d.corpus_dtype, 0);
+  p->ws_noalloc = hs::score_workspace_bytes(p->cap, d.n_corpus, d.dim, d.k, d.corpus_dtype,
+                                            hs::noalloc_scratch_bytes());
   p->ws_prio = hs::priority_workspace_bytes(p->cap);
   p->ws_total = p->ws_dedup > p->ws_score ? p->ws_dedup : p->ws_score;
   if (p->ws_prio > p->ws_total) p->ws_total = p->ws_prio;
@@ -281,7 +285,7 @@ hs_status hs_score_partial(const hs_plan *plan, const void *q_unique, int64_t n_
   const hs_merge_desc &d = plan->d;
   hipError_t e = hs::launch_score_partial(q_unique, corpus, row_scale, d.n_corpus, d.dim, d.k,
                                           n_unique, n_unique_dev, plan->cap, d.corpus_dtype,
-                                          (d.flags & HS_FLAG_TILED_CORPUS) != 0, ws,
+                                          (d.flags & HS_FLAG_TILED_CORPUS) != 0, 0, ws,
                                           (hipStream_t)stream);
   return device_status(e, "hs_score_partial launch");
 }
@@ -299,8 +303,8 @@ hs_status hs_topk_merge(const hs_plan *plan, int64_t n_unique, const int64_t *n_
   s = check_score_ws(plan, ws, ws_bytes, "hs_topk_merge");
   if (s != HS_OK) return s;
   const hs_merge_desc &d = plan->d;
-  hipError_t e = hs::launch_topk_merge(ws, n_unique, n_unique_dev, plan->cap, d.n_corpus, d.k,
-                                       d.corpus_dtype, topk_score, topk_index,
+  hipError_t e = hs::launch_topk_merge(ws, n_unique, n_unique_dev, plan->cap, d.n_corpus, d.dim,
+                                       d.k, d.corpus_dtype, 0, topk_score, topk_index,
                                        (hipStream_t)stream);
   return device_status(e, "hs_topk_merge launch");
 }
@@ -330,11 +334,11 @@ hs_status hs_score_topk_noalloc(const hs_plan *plan, const void *q_unique, int64
                                 void *stream) {
   if (!plan) return fail(HS_ERR_INVALID_ARG, "hs_score_topk_noalloc: null plan");
   const size_t cap_bytes = hs::noalloc_scratch_bytes();
-  if (plan->ws_score > cap_bytes)
+  if (plan->ws_noalloc > cap_bytes)
     return fail(HS_ERR_WORKSPACE,
                 "hs_score_topk_noalloc: this plan's score step needs %zu bytes of scratch, more "
                 "than the %zu bytes the library holds per GPU (use hs_score_topk with a "
-                "workspace)", plan->ws_score, cap_bytes);
+                "workspace)", plan->ws_noalloc, cap_bytes);
   // validation of everything but the workspace, before any device call
   hs_status s = check_nu(plan, n_unique, n_unique_dev, "hs_score_topk_noalloc");
   if (s != HS_OK) return s;
@@ -357,10 +361,10 @@ hs_status hs_score_topk_noalloc(const hs_plan *plan, const void *q_unique, int64
   hipStream_t st = (hipStream_t)stream;
   e = hs::launch_score_partial(q_unique, corpus, row_scale, d.n_corpus, d.dim, d.k, n_unique,
                                n_unique_dev, plan->cap, d.corpus_dtype,
-                               (d.flags & HS_FLAG_TILED_CORPUS) != 0, ws, st);
+                               (d.flags & HS_FLAG_TILED_CORPUS) != 0, cap_bytes, ws, st);
   if (e != hipSuccess) return device_status(e, "hs_score_topk_noalloc launch");
-  e = hs::launch_topk_merge(ws, n_unique, n_unique_dev, plan->cap, d.n_corpus, d.k,
-                            d.corpus_dtype, topk_score, topk_index, st);
+  e = hs::launch_topk_merge(ws, n_unique, n_unique_dev, plan->cap, d.n_corpus, d.dim, d.k,
+                            d.corpus_dtype, cap_bytes, topk_score, topk_index, st);
   return device_status(e, "hs_score_topk_noalloc launch");
 }
 

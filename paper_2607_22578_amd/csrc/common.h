@@ -89,6 +89,14 @@ __host__ __device__ __forceinline__ Split make_split(int64_t nu, int64_t N, int 
   return sp;
 }
 
+// Bound on S where the lists of all queries share `room` (query, slice) places
+// (0: no such bound).
+__host__ __device__ __forceinline__ int64_t bound_slices(int64_t smax, int64_t nu, uint32_t room) {
+  if (room == 0u || nu <= 0) return smax;
+  const int64_t s = room / (uint32_t)nu;
+  return s < 1 ? 1 : s < smax ? s : smax;
+}
+
 // Logical id of this workgroup: consecutive ids on one XCD (workgroups are
 // dispatched round-robin over the 8 XCDs; grid is a multiple of 8).
 __device__ __forceinline__ int logical_wg(int grid) {

@@ -45,16 +45,19 @@ constexpr int kMergeCutMin = 512;     // as many keys are ranked as soon as cut
 // bound over r = 1, 2, 4, ... is taken (up to kMergeThreads values in all).
 // Ranking takes m^2 LDS reads for m survivors: 960 queries, k = 50, S = 32 had
 // about a thousand with the shared threshold alone, 109 us.
+// ROOM: the lists leave room for a bounded n_u x S (without, the tiny window's merge
+// takes 0.2 of its 5.4 us less).
+template <bool ROOM>
 __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
     const uint64_t *__restrict__ part, const uint32_t *__restrict__ thr, int64_t n_unique,
     const int64_t *__restrict__ n_unique_dev, int64_t cap, int64_t N, int k, int mq, int nc,
-    int64_t smax, int grid, float *__restrict__ out_s, int32_t *__restrict__ out_i) {
+    int64_t smax, uint32_t room, int grid, float *__restrict__ out_s, int32_t *__restrict__ out_i) {
   __shared__ uint64_t buf[kMaxSK + 8];
   __shared__ uint64_t heads[kMergeThreads];
   __shared__ uint64_t head_cut;
   __shared__ int count;
   const int64_t nu = read_nu(n_unique, n_unique_dev, cap);
-  const Split sp = make_split(nu, N, mq, nc, grid, smax);
+  const Split sp = make_split(nu, N, mq, nc, grid, ROOM ? bound_slices(smax, nu, room) : smax);
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int n = (int)(sp.S * k);
   for (int64_t q = blockIdx.x; q < nu; q += gridDim.x) {
@@ -188,41 +191,46 @@ size_t mfma_qtile_offset(int64_t cap, int64_t N, int k, int grid_max);
 size_t qtile_bytes(int64_t cap, int64_t row_bytes);
 size_t mfma_part_offset(int64_t cap, int64_t N, int k, int grid_max);
 void mfma_split_params(int *mq, int *nc, int64_t *smax, int k);
-size_t f32_score_bytes(int64_t cap, int64_t N, int64_t d, int k);
-void f32_split_params(int64_t cap, int64_t N, int k, const void *ws, const uint32_t **thr, int *mq,
-                      int *nc, int64_t *smax, int *grid);
+size_t f32_score_bytes(int64_t cap, int64_t N, int64_t d, int k, size_t limit);
+void f32_split_params(int64_t cap, int64_t N, int64_t d, int k, size_t limit, const void *ws,
+                      const uint32_t **thr, int *mq, int *nc, int64_t *smax, uint32_t *room,
+                      int *grid);
 hipError_t launch_score_f32(const void *q, const void *corpus, int64_t N, int64_t d, int k,
-                            int64_t n_unique, const int64_t *nu_dev, int64_t cap, void *ws,
-                            hipStream_t st);
+                            int64_t n_unique, const int64_t *nu_dev, int64_t cap, size_t limit,
+                            void *ws, hipStream_t st);
 hipError_t launch_score_mfma(const void *q, const void *corpus, const float *scale, int64_t N,
                              int64_t d, int k, int64_t n_unique, const int64_t *nu_dev,
                              int64_t cap, bool fp8, bool tiled, void *ws, hipStream_t st);
 
-size_t score_workspace_bytes(int64_t cap, int64_t N, int64_t d, int k, int corpus_dtype) {
-  if (corpus_dtype == HS_F32) return f32_score_bytes(cap, N, d, k);
+// `limit`: bytes that the workspace should stay within where it can (0: none).  It
+// is part of the layout, so the three calls of a score step take the same.
+size_t score_workspace_bytes(int64_t cap, int64_t N, int64_t d, int k, int corpus_dtype,
+                             size_t limit) {
+  if (corpus_dtype == HS_F32) return f32_score_bytes(cap, N, d, k, limit);
   return mfma_qtile_offset(cap, N, k, kGridMax) + qtile_bytes(cap, d * 2);
 }
 
 hipError_t launch_score_partial(const void *q, const void *corpus, const float *scale, int64_t N,
                                 int64_t d, int k, int64_t n_unique, const int64_t *nu_dev,
-                                int64_t cap, int corpus_dtype, bool tiled, void *part,
-                                hipStream_t st) {
+                                int64_t cap, int corpus_dtype, bool tiled, size_t limit,
+                                void *part, hipStream_t st) {
   if (corpus_dtype != HS_F32)
     return launch_score_mfma(q, corpus, scale, N, d, k, n_unique, nu_dev, cap,
                              corpus_dtype == HS_FP8_E4M3, tiled, part, st);
-  return launch_score_f32(q, corpus, N, d, k, n_unique, nu_dev, cap, part, st);
+  return launch_score_f32(q, corpus, N, d, k, n_unique, nu_dev, cap, limit, part, st);
 }
 
 hipError_t launch_topk_merge(const void *part, int64_t n_unique, const int64_t *nu_dev,
-                             int64_t cap, int64_t N, int k, int corpus_dtype, float *out_s,
-                             int32_t *out_i, hipStream_t st) {
+                             int64_t cap, int64_t N, int64_t d, int k, int corpus_dtype,
+                             size_t limit, float *out_s, int32_t *out_i, hipStream_t st) {
   int64_t blocks = n_unique >= 0 ? n_unique : cap;
   if (blocks <= 0) return hipSuccess;
   int mq, nc, grid;
   int64_t smax;
+  uint32_t room = 0;   // (bf16 / fp8: the lists hold the worst n_u x S)
   const uint32_t *thr;
   if (corpus_dtype == HS_F32) {
-    f32_split_params(cap, N, k, part, &thr, &mq, &nc, &smax, &grid);
+    f32_split_params(cap, N, d, k, limit, part, &thr, &mq, &nc, &smax, &room, &grid);
   } else {
     grid = persistent_grid();
     mfma_split_params(&mq, &nc, &smax, k);
@@ -233,9 +241,10 @@ hipError_t launch_topk_merge(const void *part, int64_t n_unique, const int64_t *
   }
   // a persistent grid of at most two workgroups per CU loops over queries
   if (blocks > 2 * (int64_t)grid) blocks = 2 * (int64_t)grid;
-  hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)blocks), dim3(kMergeThreads), 0, st,
-                     (const uint64_t *)part, thr, n_unique, nu_dev, cap, N, k, mq, nc, smax, grid,
-                     out_s, out_i);
+  hipLaunchKernelGGL(room ? topk_merge_kernel<true> : topk_merge_kernel<false>,
+                     dim3((unsigned)blocks), dim3(kMergeThreads), 0, st,
+                     (const uint64_t *)part, thr, n_unique, nu_dev, cap, N, k, mq, nc, smax, room,
+                     grid, out_s, out_i);
   return hipGetLastError();
 }
 

@@ -485,11 +485,11 @@ __device__ __forceinline__ void run_item_f32(const MfmaArgs &a, const MLds &L, c
 }
 
 template <bool LDS_LISTS, bool SEED>
-__global__ __launch_bounds__(kFT, 2) void score_f32_mfma(MfmaArgs a, int64_t smax) {
+__global__ __launch_bounds__(kFT, 2) void score_f32_mfma(MfmaArgs a, int64_t smax, uint32_t room) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const MLds L = carve_flds(smem, a.k);
   const int64_t nu = read_nu(a.n_unique, a.n_unique_dev, a.cap);
-  const Split sp = make_split(nu, a.N, kMMQ, kFNC, a.grid, smax);
+  const Split sp = make_split(nu, a.N, kMMQ, kFNC, a.grid, bound_slices(smax, nu, room));
   if (SEED && !f32_seeded(sp)) return;
   const int items = (int)(sp.qtiles * sp.S);
   if (threadIdx.x < 4) L.flags[threadIdx.x] = 0;
@@ -508,78 +508,106 @@ __global__ __launch_bounds__(kFT, 2) void score_f32_mfma(MfmaArgs a, int64_t sma
 // ---------------------------------------------------------------- host side
 
 int persistent_grid();
-hipError_t launch_seed_select(const MfmaArgs &a, int64_t smax, bool f32, hipStream_t st);
+hipError_t launch_seed_select(const MfmaArgs &a, int64_t smax, uint32_t room, bool f32,
+                              hipStream_t st);
 size_t qtile_bytes(int64_t cap, int64_t row_bytes);
 hipError_t launch_tile_queries(const void *q, int64_t n_unique, const int64_t *nu_dev, int64_t cap,
                                int64_t row_bytes, void *dst, hipStream_t st);
 
 // Workspace: [partial lists, n_u x S x k keys; the seed pass's group maxima,
 // n_u x min(S, 256) x 8 u32, use the same bytes before them][shared
-// thresholds, cap x u32][tiled queries].  It stays within 64 MiB, the size of
-// the library's own scratch, wherever one slice per query does: the lists take
-// at most 40 MiB of it (S is limited to that, or to 1), there is no seed
-// without room for the thresholds and no tiled copy of the queries without
-// room for that (nor for up to 32 queries, where its launch costs more than it
-// saves).
-constexpr size_t kFBudget = (size_t)64 << 20, kFListBudget = (size_t)40 << 20;
+// thresholds, cap x u32][tiled queries].
+//
+// The lists have room for a number of (query, slice) places, and a call takes as
+// many slices as its own n_u leaves room for (bound_slices): a plan made for many
+// requests of which few are distinct fills the chip like one made for those few.
+// The room is what kFRounds rounds of items on 256 CUs take, or 40 MiB, or a slice
+// per query, whichever is most, and no more than every slice of every query.
+//
+// Within a limit (the library's own scratch; 0: none) the room shrinks to what is
+// left, and the tiled queries go where they do not fit beside one round or 40 MiB
+// of lists, and the seed where its thresholds do not fit beside a slice per query.
+// (No tiled queries either for up to 32 of them, where the copy's launch costs more
+// than it saves, nor above 256 MiB.)
+constexpr size_t kFListBudget = (size_t)40 << 20, kFTiledMax = (size_t)256 << 20;
+constexpr int kFCus = 256, kFRounds = 4;
 
 struct F32Layout {
-  int64_t smax;
-  bool seed;
-  size_t thr_at, q_at;
+  int64_t smax;    // bound on S for any n_u
+  uint32_t room;   // and on n_u x S (0: none)
+  bool seed, tiled;
+  size_t thr_at, q_at, bytes;
 };
 
-static F32Layout f32_layout(int64_t cap, int64_t N, int k) {
+static F32Layout f32_layout(int64_t cap, int64_t N, int64_t d, int k, size_t limit) {
   F32Layout l;
-  const size_t c = (size_t)(cap > 0 ? cap : 1);
-  const size_t per = (size_t)(k < 4 ? 4 : k) * 8;   // bytes of a query and slice, maxima included
-  const size_t thr = (c * 4 + 255) & ~(size_t)255;
-  l.seed = c * per + thr + 256 <= kFBudget;
-  int64_t s = l.seed ? (int64_t)(kFListBudget / (c * per)) : 1;
+  auto round = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const int64_t c = cap > 0 ? cap : 1;
+  const size_t keys = (size_t)k * 8, per = (size_t)(k < 4 ? 4 : k) * 8;   // (maxima included)
+  const size_t thr = round((size_t)c * 4), qt = c > 32 ? qtile_bytes(c, d * 4) : 0;
   const int64_t most = kMSplitMaxSK / k < 1 ? 1 : kMSplitMaxSK / k;
   const int64_t tiles = (N + kFNC - 1) / kFNC;
-  s = s < most ? s : most;
-  s = s < tiles ? s : tiles;
-  l.smax = s < 1 ? 1 : s;
-  l.thr_at = (c * (size_t)l.smax * (l.seed ? per : (size_t)k * 8) + 255) & ~(size_t)255;
+  l.smax = most < tiles ? most : tiles < 1 ? 1 : tiles;
+  auto places = [&](int64_t r) { return r < c ? c : r < c * l.smax ? r : c * l.smax; };
+  auto want = [&](size_t p) {
+    const int64_t r = (int64_t)(kFListBudget / p);
+    return places(r > kFRounds * kFCus * kMMQ ? r : kFRounds * kFCus * kMMQ);
+  };
+  l.seed = true;
+  l.tiled = qt > 0 && qt <= kFTiledMax;
+  size_t p = per;
+  int64_t room = want(p);
+  if (limit && round((size_t)room * p) + thr + (l.tiled ? qt : 0) > limit) {
+    l.seed = round((size_t)c * per) + thr <= limit;
+    if (!l.seed) p = keys;
+    size_t left = limit - (l.seed ? thr : 0);
+    const size_t one = (size_t)places(kFCus * kMMQ) * p, least = (size_t)c * p;
+    const size_t beside = one < kFListBudget ? one : kFListBudget > least ? kFListBudget : least;
+    l.tiled = l.tiled && round(beside) + qt <= left;
+    if (l.tiled) left -= qt;
+    const int64_t fits = (int64_t)(left / p), w = want(p);
+    room = places(fits < w ? fits : w);
+  }
+  l.room = room < c * l.smax ? (uint32_t)room : 0u;   // (0: every slice of every query)
+  l.thr_at = round((size_t)room * p);
   l.q_at = l.thr_at + (l.seed ? thr : 0);
+  l.bytes = l.q_at + (l.tiled ? qt : 0);
   return l;
 }
 
-static bool f32_tiled(const F32Layout &l, int64_t cap, int64_t d) {
-  return cap > 32 && l.q_at + qtile_bytes(cap, d * 4) <= kFBudget;
-}
-
-size_t f32_score_bytes(int64_t cap, int64_t N, int64_t d, int k) {
-  const F32Layout l = f32_layout(cap, N, k);
-  return l.q_at + (f32_tiled(l, cap, d) ? qtile_bytes(cap, d * 4) : 0);
+size_t f32_score_bytes(int64_t cap, int64_t N, int64_t d, int k, size_t limit) {
+  return f32_layout(cap, N, d, k, limit).bytes;
 }
 
 // What topk_merge_kernel needs to find this path's lists: thresholds (null:
-// none), the bound on S and the tile sizes.
-void f32_split_params(int64_t cap, int64_t N, int k, const void *ws, const uint32_t **thr, int *mq,
-                      int *nc, int64_t *smax, int *grid) {
-  const F32Layout l = f32_layout(cap, N, k);
+// none), the bounds on S and the tile sizes.
+void f32_split_params(int64_t cap, int64_t N, int64_t d, int k, size_t limit, const void *ws,
+                      const uint32_t **thr, int *mq, int *nc, int64_t *smax, uint32_t *room,
+                      int *grid) {
+  const F32Layout l = f32_layout(cap, N, d, k, limit);
   *mq = kMMQ;
   *nc = kFNC;
   *smax = l.smax;
+  *room = l.room;
   *grid = persistent_grid();
-  *thr = l.seed && f32_seeded(make_split(cap, N, kMMQ, kFNC, *grid, l.smax))
+  *thr = l.seed && f32_seeded(make_split(cap, N, kMMQ, kFNC, *grid,
+                                         bound_slices(l.smax, cap, l.room)))
              ? (const uint32_t *)((const unsigned char *)ws + l.thr_at)
              : nullptr;
 }
 
-template <typename K>
-static hipError_t launch_f32(K kern, const MfmaArgs &a, int64_t smax, hipStream_t st) {
+template <bool LDS_LISTS, bool SEED>
+static hipError_t launch_f32(const MfmaArgs &a, int64_t smax, uint32_t room, hipStream_t st) {
+  const auto kern = score_f32_mfma<LDS_LISTS, SEED>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, f32_lds_bytes());
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(a.grid), dim3(kFT), f32_lds_bytes(), st, a, smax);
+  hipLaunchKernelGGL(kern, dim3(a.grid), dim3(kFT), f32_lds_bytes(), st, a, smax, room);
   return hipGetLastError();
 }
 
 hipError_t launch_score_f32(const void *q, const void *corpus, int64_t N, int64_t d, int k,
-                            int64_t n_unique, const int64_t *nu_dev, int64_t cap, void *ws,
+                            int64_t n_unique, const int64_t *nu_dev, int64_t cap, size_t limit, void *ws,
                             hipStream_t st) {
   MfmaArgs a = {};
   a.q = q;
@@ -595,10 +623,11 @@ hipError_t launch_score_f32(const void *q, const void *corpus, int64_t N, int64_
   const uint32_t *thr;
   int mq, nc;
   int64_t smax;
-  f32_split_params(cap, N, k, ws, &thr, &mq, &nc, &smax, &a.grid);
+  uint32_t room;
+  f32_split_params(cap, N, d, k, limit, ws, &thr, &mq, &nc, &smax, &room, &a.grid);
   a.gthr = const_cast<uint32_t *>(thr);
-  const F32Layout l = f32_layout(cap, N, k);
-  if (f32_tiled(l, cap, d)) {
+  const F32Layout l = f32_layout(cap, N, d, k, limit);
+  if (l.tiled) {
     void *qt = (unsigned char *)ws + l.q_at;
     hipError_t e = launch_tile_queries(q, n_unique, nu_dev, cap, d * 4, qt, st);
     if (e != hipSuccess) return e;
@@ -609,13 +638,13 @@ hipError_t launch_score_f32(const void *q, const void *corpus, int64_t N, int64_
   if (thr) {
     // (fewer queries make more and shorter slices: a call may still turn out
     // to be unseeded on the device, which then clears its thresholds)
-    hipError_t e = launch_f32(score_f32_mfma<false, true>, a, smax, st);
+    hipError_t e = launch_f32<false, true>(a, smax, room, st);
     if (e != hipSuccess) return e;
-    e = launch_seed_select(a, smax, true, st);
+    e = launch_seed_select(a, smax, room, true, st);
     if (e != hipSuccess) return e;
   }
-  return ll ? launch_f32(score_f32_mfma<true, false>, a, smax, st)
-            : launch_f32(score_f32_mfma<false, false>, a, smax, st);
+  return ll ? launch_f32<true, false>(a, smax, room, st)
+            : launch_f32<false, false>(a, smax, room, st);
 }
 
 }  // namespace hs

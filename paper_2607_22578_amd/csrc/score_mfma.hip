@@ -1421,13 +1421,15 @@ constexpr int kSeedThreads = 256;
 template <bool F32>
 __global__ __launch_bounds__(kSeedThreads) void mfma_seed_kernel(
     const uint32_t *__restrict__ lmax, int64_t n_unique, const int64_t *__restrict__ nu_dev,
-    int64_t cap, int64_t N, int nch, int k, int64_t smax, int grid, uint32_t *__restrict__ gthr,
+    int64_t cap, int64_t N, int nch, int k, int64_t smax, uint32_t room, int grid,
+    uint32_t *__restrict__ gthr,
     uint32_t *__restrict__ lvl) {
   __shared__ uint32_t vals[kSeedMax];
   __shared__ uint32_t hist[256];
   __shared__ uint32_t sel[2];   // chosen digit, values above it
   const int64_t nu = read_nu(n_unique, nu_dev, cap);
-  const Split sp = make_split(nu, N, kMMQ, F32 ? kFNC : kMNC, grid, smax);
+  const Split sp =
+      make_split(nu, N, kMMQ, F32 ? kFNC : kMNC, grid, bound_slices(smax, nu, room));
   int64_t per;
   if (F32) {
     const int64_t stride = f32_seed_stride(sp.S);
@@ -1501,14 +1503,15 @@ __global__ __launch_bounds__(kSeedThreads) void mfma_seed_kernel(
   }
 }
 
-hipError_t launch_seed_select(const MfmaArgs &a, int64_t smax, bool f32, hipStream_t st) {
+hipError_t launch_seed_select(const MfmaArgs &a, int64_t smax, uint32_t room, bool f32,
+                              hipStream_t st) {
   const int64_t want = a.n_unique >= 0 ? a.n_unique : a.cap;
   const int64_t blocks = want < 4 * (int64_t)a.grid ? want : 4 * (int64_t)a.grid;
   if (blocks <= 0) return hipSuccess;
   hipLaunchKernelGGL(f32 ? mfma_seed_kernel<true> : mfma_seed_kernel<false>,
                      dim3((unsigned)blocks), dim3(kSeedThreads), 0, st, a.lmax, a.n_unique,
-                     a.n_unique_dev, a.cap, a.N, (int)((a.d + kMKC - 1) / kMKC), a.k, smax, a.grid,
-                     a.gthr, a.lvl);
+                     a.n_unique_dev, a.cap, a.N, (int)((a.d + kMKC - 1) / kMKC), a.k, smax, room,
+                     a.grid, a.gthr, a.lvl);
   return hipGetLastError();
 }
 
@@ -1673,7 +1676,7 @@ hipError_t launch_score_mfma(const void *q, const void *corpus, const float *sca
   e = run(true);
   if (e != hipSuccess) return e;
   int64_t smax = kMSplitMaxSK / k;
-  e = launch_seed_select(a, smax < 1 ? 1 : smax, false, st);
+  e = launch_seed_select(a, smax < 1 ? 1 : smax, 0u, false, st);
   if (e != hipSuccess) return e;
   return run(false);
 }

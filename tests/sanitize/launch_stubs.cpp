@@ -15,7 +15,7 @@ int hs_stub_launches = 0;
 namespace hs {
 struct CacheView;
 size_t dedup_workspace_bytes(int64_t R) { return R <= 4096 ? 0 : (size_t)R * 32; }
-size_t score_workspace_bytes(int64_t cap, int64_t N, int64_t d, int k, int) {
+size_t score_workspace_bytes(int64_t cap, int64_t N, int64_t d, int k, int, size_t) {
   (void)N;
   (void)d;
   return ((size_t)cap * (size_t)k * 64 + 255) & ~(size_t)255;
@@ -44,10 +44,10 @@ HS_STUB(launch_gather, const void *, int64_t, int64_t, const void *, int, int64_
 HS_STUB(launch_deliver, const float *, const int32_t *, int64_t, const int32_t *, int64_t, int,
         float *, int32_t *, hipStream_t)
 HS_STUB(launch_score_partial, const void *, const void *, const float *, int64_t, int64_t, int,
-        int64_t, const int64_t *, int64_t, int, bool, void *, hipStream_t)
+        int64_t, const int64_t *, int64_t, int, bool, size_t, void *, hipStream_t)
 HS_STUB(launch_tile_corpus, const void *, int64_t, int64_t, bool, void *, hipStream_t)
-HS_STUB(launch_topk_merge, const void *, int64_t, const int64_t *, int64_t, int64_t, int, int,
-        float *, int32_t *, hipStream_t)
+HS_STUB(launch_topk_merge, const void *, int64_t, const int64_t *, int64_t, int64_t, int64_t, int,
+        int, size_t, float *, int32_t *, hipStream_t)
 HS_STUB(launch_cache_reset, void *, int64_t, int, hipStream_t)
 HS_STUB(launch_cache_lookup, void *, int64_t, int, const int64_t *, const int32_t *, int64_t,
         const int64_t *, int64_t, float *, int32_t *, int32_t *, int32_t *, int64_t *,

@@ -79,3 +79,69 @@ def test_f32_infinite_and_nan_rows(n, k):
         exact = c[finite].astype(np.float64) @ q[u].astype(np.float64)
         order = finite[np.argsort(-exact, kind="stable")][:k - 1]
         np.testing.assert_array_equal(i[u][1:], order)
+
+
+def _score_ms(requests, nu, n, d, k, runs=5):
+    """Shortest of a few hs_score_topk calls on nu distinct queries, in ms."""
+    import paper_2607_22578_amd as hs
+    m = hs.MergedRetrieval(requests, d, n, k, hs.HS_F32, hs.HS_F32, device=device())
+    g = torch.Generator(device=device())
+    g.manual_seed(n)
+    q, c = (torch.randn(r, d, device=device(), generator=g) for r in (nu, n))
+    m.q_unique[:nu].copy_(q)
+    best = float("inf")
+    for _ in range(runs):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        hs.hs_score_topk(m.plan, m.q_unique, nu, None, c, None, m.topk_score, m.topk_index, m.ws)
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best, m.topk_index[:nu].cpu().numpy()
+
+
+@pytest.mark.parametrize("requests,nu,k", [(8_192, 100, 40), (8_192, 300, 40), (32_768, 400, 10),
+                                           (200_000, 500, 10)])
+def test_f32_many_requests_few_distinct_run_like_the_distinct_alone(requests, nu, k):
+    # the slices follow from the distinct queries, not from the plan's requests (which
+    # left 8 to 64 of the workgroups with work and took 3 to 30 times as long)
+    note(f"fp32 R={requests} n_u={nu} k={k}")
+    alone, want = _score_ms(nu, nu, 100_000, 128, k)
+    many, got = _score_ms(requests, nu, 100_000, 128, k)
+    np.testing.assert_array_equal(got, want)
+    assert many < 1.5 * alone + 0.03, f"{many * 1e3:.0f} us, alone {alone * 1e3:.0f} us"
+
+
+# plans whose lists leave room for a few slices only, for the thresholds but no tiled
+# queries, for neither (fewer than four keys per list: the maxima would not fit), and
+# for a slice per query, in the 64 MiB of the allocation-free entry point; the same
+# plans with a workspace of their own, scored in two orders of the calls
+@pytest.mark.parametrize("requests,nu,n,d,k", [
+    (8_192, 90, 20_011, 64, 40), (100_000, 140, 20_011, 1_024, 10), (2_100_000, 70, 9_001, 32, 3),
+    (8_000, 300, 9_001, 36, 1_000), (200_000, 1_500, 9_001, 32, 33),
+])
+def test_f32_plans_with_little_room(requests, nu, n, d, k):
+    import paper_2607_22578_amd as hs
+    note(f"fp32 R={requests} n_u={nu} N={n} d={d} k={k}")
+    q, c = _rows(nu, d, 207), _rows(n, d, 208)
+    dev = device()
+    plan = hs.hs_merge_plan(requests, d, n, k, hs.HS_F32, hs.HS_F32)
+    ws = torch.full((plan.workspace_bytes,), 0xA5, dtype=torch.uint8, device=dev)
+    qd, cd = to_dev(q), to_dev(c)
+    nu_dev = torch.tensor([nu], dtype=torch.int64, device=dev)
+
+    class Out:
+        pass
+
+    ref = {"n_unique": nu, "first_index": np.arange(nu, dtype=np.int32)}
+    for noalloc, count in ((True, nu), (False, nu), (False, -1), (True, -1)):
+        m = Out()
+        m.topk_score = torch.full((nu, k), 7.0, device=dev)
+        m.topk_index = torch.full((nu, k), -7, dtype=torch.int32, device=dev)
+        args = (plan, qd, count, nu_dev, cd, None, m.topk_score, m.topk_index)
+        if noalloc:
+            hs.hs_score_topk_noalloc(*args)
+        else:
+            hs.hs_score_topk(*args, ws)
+        torch.cuda.synchronize()
+        check_unique_topk(m, ref, q, c, k, sel=np.unique(np.linspace(0, nu - 1, 24).astype(int)))
