@@ -186,7 +186,6 @@ int persistent_grid() {
   return cache[dev] < kGridMax ? cache[dev] : kGridMax;
 }
 
-size_t mfma_partial_bytes(int64_t cap, int64_t N, int k, int grid_max);
 size_t mfma_qtile_offset(int64_t cap, int64_t N, int k, int grid_max);
 size_t qtile_bytes(int64_t cap, int64_t row_bytes);
 size_t mfma_part_offset(int64_t cap, int64_t N, int k, int grid_max);

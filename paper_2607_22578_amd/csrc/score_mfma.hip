@@ -97,13 +97,11 @@ constexpr int kMLanesQ = kMW * 2;        // lanes holding one query in a tile
 // - Longer slices: their own lists and the bounds they publish take over.  One
 //   tile for k <= 48 (8 or 16 changed nothing at k = 32, n = 651, S = 16); for
 //   larger k the lists fill late, and T grows to 20 within 1/16 of the slice.
+// The maxima share the lists' bytes, 32 T against 8 k per query and slice, and T
+// stays within k / 4 for short slices: many queries run as short slices, and
+// their lists are what a workspace is sized by.
 constexpr int kSeedMax = 16384;
 constexpr int kSeedTilesMax = 20;
-// the most for any shape (the maxima share the lists' bytes: 32 T against 8 k
-// bytes per query and slice)
-__host__ __device__ __forceinline__ int seed_tiles_max(int k) {
-  return k > 48 ? kSeedTilesMax : k < 8 ? 1 : k / 4;
-}
 __host__ __device__ __forceinline__ int seed_tiles(int k, int64_t ntiles, int64_t S, int nch) {
   if (S < 1) return 1;
   const int n = (int)(ntiles / S);
@@ -114,12 +112,13 @@ __host__ __device__ __forceinline__ int seed_tiles(int k, int64_t ntiles, int64_
     const int64_t num = 60 * (int64_t)k * n, den = S * (10 * (int64_t)nch + 16);
     while (t < kSeedTilesMax && (int64_t)(2 * t + 1) * (2 * t + 1) * den <= 4 * num) ++t;
     if (t > n / 2) t = n / 2;
+    if (t > k / 4) t = k / 4;   // (within the lists' bytes)
   } else if (k > 48) {
     t = n / 16;
   }
   const int room = (int)(kSeedMax / (S * kMLanesQ));
   if (t > room) t = room;
-  if (t > seed_tiles_max(k)) t = seed_tiles_max(k);
+  if (t > kSeedTilesMax) t = kSeedTilesMax;
   return t < 1 ? 1 : t;
 }
 // Slices that take part in the seed sample: one in every seed_stride(S), at
@@ -1329,8 +1328,17 @@ int persistent_grid();
 // (rounded to 256 bytes) followed by the partial lists.
 size_t mfma_thr_bytes(int64_t cap) { return ((size_t)cap * 4 + 255) & ~(size_t)255; }
 
+// Bytes of a query and slice in the partial-list area: the list, or the seed
+// pass's maxima where these take more.  (The sample of short slices, the only one
+// that depends on the dimension, is held within the list's bytes.)
+static size_t mfma_list_bytes(int k, const Split &sp) {
+  const size_t lists = (size_t)k * 8;
+  const size_t maxima = (size_t)seed_tiles(k, sp.ntiles, sp.S, 1) * kMLanesQ * 4;
+  return lists > maxima ? lists : maxima;
+}
+
 // worst case over n_u in [1, cap] and grids up to grid_max of n_u * S *
-// per_slice bytes.
+// per_slice bytes (0: those of the partial-list area).
 // It takes up to (cap / 128) x 64 splits, and every score call lays out its
 // workspace with it, so results are kept for the few shapes a process uses
 // (on a window of a few hundred queries the loops cost tens of microseconds,
@@ -1362,7 +1370,8 @@ static size_t mfma_split_worst(int64_t cap, int64_t N, int k, int grid_max, size
     const int64_t nu = qt * kMMQ < cap ? qt * kMMQ : cap;
     for (int64_t g = 8; g <= grid_max; g += 8) {
       const Split sp = make_split(nu, N, kMMQ, kMNC, g, smax);
-      const size_t b = (size_t)nu * (size_t)sp.S * per_slice;
+      const size_t b =
+          (size_t)nu * (size_t)sp.S * (per_slice ? per_slice : mfma_list_bytes(k, sp));
       if (b > best) best = b;
     }
   }
@@ -1386,10 +1395,8 @@ size_t mfma_part_offset(int64_t cap, int64_t N, int k, int grid_max) {
   return mfma_thr_bytes(cap) + mfma_lvl_bytes(cap, N, k, grid_max);
 }
 
-size_t mfma_partial_bytes(int64_t cap, int64_t N, int k, int grid_max) {
-  const size_t lists = (size_t)k * 8, maxima = (size_t)seed_tiles_max(k) * kMLanesQ * 4;
-  return mfma_part_offset(cap, N, k, grid_max) +
-         mfma_split_worst(cap, N, k, grid_max, lists > maxima ? lists : maxima);
+static size_t mfma_partial_bytes(int64_t cap, int64_t N, int k, int grid_max) {
+  return mfma_part_offset(cap, N, k, grid_max) + mfma_split_worst(cap, N, k, grid_max, 0);
 }
 
 void mfma_split_params(int *mq, int *nc, int64_t *smax, int k) {

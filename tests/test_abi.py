@@ -329,3 +329,18 @@ def test_noalloc_validation():
         with pytest.raises(hs.HsError) as e:
             hs.hs_score_topk_noalloc(p, *args)
         assert e.value.status == code, args
+
+
+@pytest.mark.parametrize("R,d,N,k,dtype", [(936, 448, 187_300, 49, "HS_BF16"),
+                                           (1_024, 256, 50_000, 50, "HS_BF16"),
+                                           (4_096, 256, 10_000, 64, "HS_BF16"),
+                                           (1_678, 16, 27_769, 52, "HS_BF16"),
+                                           (6_110, 144, 8_103, 51, "HS_FP8_E4M3")])
+def test_noalloc_takes_plans_whose_lists_fit(R, d, N, k, dtype):
+    # the seed sample's maxima take no more than the lists where slices are short: these
+    # plans' lists, bounds and queries need 45 to 62 MiB.  (n_unique is checked after the
+    # scratch size: an invalid count tells that the plan was not refused.)
+    p = hs.hs_merge_plan(R, d, N, k, hs.HS_BF16, getattr(hs, dtype))
+    with pytest.raises(hs.HsError) as e:
+        hs.hs_score_topk_noalloc(p, FAKE, R + 1, None, FAKE, FAKE, FAKE, FAKE)
+    assert e.value.status == hs.HS_ERR_INVALID_ARG, hs.hs_last_error()
