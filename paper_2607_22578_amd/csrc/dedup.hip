@@ -314,10 +314,10 @@ constexpr int kBarGroups = 16;        // arrival counters of the grid barrier
 constexpr int kCtlStride = 32;        // 32-bit words between counters (128 B)
 // control words: [0] value-block ticket of the groups launch; [kCtlFull] set
 // when the hash path has given up (a bucket is full, or a search too long);
-// [kCtlSpread] the sampled keys suit the hash path; barrier arrival counter j at (1 + j) * kCtlStride; the barrier's release counter at
+// barrier arrival counter j at (1 + j) * kCtlStride; the barrier's release counter at
 // (1 + kBarGroups) * kCtlStride
 constexpr int kCtlWords = (2 + kBarGroups) * kCtlStride;
-constexpr int kCtlFull = 1, kCtlSpread = 2;
+constexpr int kCtlFull = 1;
 constexpr int kSampleKeys = 1024;   // the first keys of the window
 
 struct RadixWs {
@@ -327,6 +327,7 @@ struct RadixWs {
   uint64_t *range;         // [0] = global min, [1] = radix pass count,
                            // [2] = key values of the dense path (0: others),
                            // [3] = hash path, [4] = range of the sampled keys
+                           // where they suit that path (else 0)
   uint32_t *hist;          // kBins x nb, digit-major (scanned in place)
   uint32_t *dtot;          // kBins digit totals of a pass
   uint32_t *bheads;        // heads per tile (scanned in place)
@@ -452,7 +453,13 @@ __device__ __forceinline__ uint32_t hash_of(uint64_t m, int bits) {
 // (36 are usual for 1,024 keys in 2,048 slots) tells keys that the hash does not
 // spread.
 constexpr uint64_t kSpreadMax = 768;
-__device__ void sample_spread(const int64_t *__restrict__ keys, int R, const RadixWs &ws) {
+//
+// Workgroup e of E: the first decides, the others clear the table and the bucket
+// counts if the keys lie far enough apart.  They are not the workgroups that read
+// the keys: 256 of those, each reading the same 8 KiB for this, took the dense path
+// 1 us longer (262,144 ids and the gather of their rows: 86.5 us).
+__device__ void sample_spread(const int64_t *__restrict__ keys, int R, const RadixWs &ws, int e0,
+                              int E) {
   constexpr int per = kSampleKeys / kRadixThreads, slots = 2 * kSampleKeys, W = kRadixThreads / 64;
   constexpr int lbits = 11, kBucketsMax = 1 << 12;
   static_assert(slots == 1 << lbits && kHashRMax == 1 << 20, "sample table, buckets of 2^20 keys");
@@ -468,9 +475,11 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
     mn = m[e] < mn ? m[e] : mn;
     mx = m[e] > mx ? m[e] : mx;
   }
-  for (int i = tid; i < slots; i += kRadixThreads) set[i] = 0ull;
-  for (int i = tid; i < 1 << bucket_bits(ws.hbits); i += kRadixThreads) cnt[i] = 0u;
-  if (tid == 0) total = longer = 0u;
+  if (e0 == 0) {
+    for (int i = tid; i < slots; i += kRadixThreads) set[i] = 0ull;
+    for (int i = tid; i < 1 << bucket_bits(ws.hbits); i += kRadixThreads) cnt[i] = 0u;
+    if (tid == 0) total = longer = 0u;
+  }
   for (int o = 32; o > 0; o >>= 1) {
     const uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
     mn = a < mn ? a : mn;
@@ -487,7 +496,17 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
   }
   const uint64_t span = mx - mn;
   if (span < (uint64_t)R) {
-    if (tid == 0) ws.ctl[kCtlSpread] = 0u;
+    if (e0 == 0 && tid == 0) ws.range[4] = 0ull;
+    return;
+  }
+  if (e0 > 0) {
+    const int64_t slots = (int64_t)1 << ws.hbits, gs = (int64_t)(E - 1) * kRadixThreads;
+    for (int64_t i = (int64_t)(e0 - 1) * kRadixThreads + tid; i <= slots; i += gs) {
+      if (i < slots) ws.hk[i] = 0ull;
+      ws.hfirst[i] = 0u;
+      ws.hcnt[i] = 0u;
+      if (i < ((int64_t)1 << bucket_bits(ws.hbits))) ws.bcnt[i] = 0u;
+    }
     return;
   }
   const int shift = bucket_shift(span, ws.hbits);
@@ -519,8 +538,7 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
   if (tid == 0) {
     const uint64_t n = total >> 21, pairs = total & ((1u << 21) - 1u);
     const bool fit = longer == 0u && (uint64_t)R * pairs <= kSpreadMax * kSampleKeys * n;
-    ws.ctl[kCtlSpread] = fit ? 1u : 0u;
-    ws.range[4] = span;
+    ws.range[4] = fit ? span : 0ull;
   }
 }
 
@@ -530,11 +548,11 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
 // their neutral values.
 constexpr int kPrepChunk = 4 * kRadixThreads;
 __global__ __launch_bounds__(kRadixThreads) void dedup_prep_kernel(
-    const int64_t *__restrict__ keys, int R, RadixWs ws) {
+    const int64_t *__restrict__ keys, int R, int P, RadixWs ws) {
   __shared__ uint64_t smin[kRadixThreads / 64], smax[kRadixThreads / 64];
-  const int tid = threadIdx.x, P = gridDim.x - (ws.hbits ? 1 : 0);
-  if ((int)blockIdx.x == P) {
-    sample_spread(keys, R, ws);
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x >= P) {   // (hash path only)
+    sample_spread(keys, R, ws, (int)blockIdx.x - P, (int)gridDim.x - P);
     return;
   }
   uint64_t mn = ~0ull, mx = 0ull;
@@ -552,7 +570,7 @@ __global__ __launch_bounds__(kRadixThreads) void dedup_prep_kernel(
     }
   }
   for (int o = 32; o > 0; o >>= 1) {
-    uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
+    const uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
     mn = a < mn ? a : mn;
     mx = c > mx ? c : mx;
   }
@@ -580,58 +598,15 @@ __global__ __launch_bounds__(kRadixThreads) void dedup_prep_kernel(
   const int64_t nvb = ((int64_t)R + 1023) / 1024;
   for (int64_t i = gt; i < nvb; i += gs) ws.flags[i] = 0ull;
   if (blockIdx.x == 0)
-    for (int i = tid; i < kCtlWords; i += kRadixThreads)
-      if (i != kCtlSpread) ws.ctl[i] = 0u;
-  // The hash path is taken only where the first 1,024 keys already lie R or
-  // more apart, which every workgroup here can tell (so the dense path, whose
-  // keys do not, pays nothing for it): each then clears its share of the table
-  // and the bucket counts.  The last workgroup decides from the same keys
-  // whether they suit the path.
-  if (!ws.hbits) return;
-  __shared__ int wide;
-  mn = ~0ull;
-  mx = 0ull;
-#pragma unroll
-  for (int e = 0; e < kSampleKeys / kRadixThreads; ++e) {
-    const uint64_t k = map_key(keys[e * kRadixThreads + tid]);   // (R > kSmallMax)
-    mn = k < mn ? k : mn;
-    mx = k > mx ? k : mx;
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
-    mn = a < mn ? a : mn;
-    mx = c > mx ? c : mx;
-  }
-  __syncthreads();   // (thread 0 has read the first reduction's words)
-  if ((tid & 63) == 0) {
-    smin[tid >> 6] = mn;
-    smax[tid >> 6] = mx;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < kRadixThreads / 64; ++w) {
-      mn = smin[w] < mn ? smin[w] : mn;
-      mx = smax[w] > mx ? smax[w] : mx;
-    }
-    wide = mx - mn >= (uint64_t)R;
-  }
-  __syncthreads();
-  if (!wide) return;
-  const int64_t slots = (int64_t)1 << ws.hbits;
-  for (int64_t i = gt; i <= slots; i += gs) {
-    if (i < slots) ws.hk[i] = 0ull;
-    ws.hfirst[i] = 0u;
-    ws.hcnt[i] = 0u;
-    if (i < ((int64_t)1 << bucket_bits(ws.hbits))) ws.bcnt[i] = 0u;
-  }
+    for (int i = tid; i < kCtlWords; i += kRadixThreads) ws.ctl[i] = 0u;
 }
 
 struct Range {
   uint64_t mn;
   uint64_t npass;   // radix passes (0 on the dense path)
   uint64_t nv;      // key values of the dense path (0: others)
-  int hash;         // hash path: keys - mn >> hash_shift is the bucket
-  int hash_shift;
+  int hash;         // hash path
+  uint64_t span;    // max - min
 };
 
 // Global min/max over the P prep partials and the path: dense when the keys
@@ -642,8 +617,6 @@ __device__ Range range_of(int R, int P, const RadixWs &ws) {
   __shared__ uint64_t smin[kRadixThreads / 64], smax[kRadixThreads / 64];
   __shared__ Range res;
   const int tid = threadIdx.x;
-  const bool spread = ws.hbits && ws.ctl[kCtlSpread] != 0u;
-  const uint64_t sample = ws.range[4];   // (written where spread)
   uint64_t mn = ~0ull, mx = 0ull;
   for (int i = tid; i < P; i += kRadixThreads) {
     mn = ws.pmin[i] < mn ? ws.pmin[i] : mn;
@@ -670,9 +643,10 @@ __device__ Range range_of(int R, int P, const RadixWs &ws) {
     res.mn = mn;
     res.npass = dense ? 0ull : (uint64_t)((bits + kRadixBits - 1) / kRadixBits);
     res.nv = dense ? span + 1 : 0ull;
-    // (a range of twice the sample's or more has keys that the sample did not see)
-    res.hash = !dense && spread && span >> 1 <= sample ? 1 : 0;
-    res.hash_shift = dense ? 0 : bucket_shift(span, ws.hbits);
+    // (a range of twice the sample's or more has keys that the sample did not see;
+    // the dense path does not wait for the word)
+    res.hash = !dense && ws.hbits && span >> 1 <= ws.range[4] ? 1 : 0;
+    res.span = span;
   }
   __syncthreads();
   return res;
@@ -700,13 +674,14 @@ constexpr int kAggRound = 1024, kAggSlots = 2048;
 // request's slot.  Bound by the latency of a few dependent device-scope
 // atomics per key.  Once any workgroup has given up (kCtlFull) the others do no
 // more than they have begun.
-__device__ void hash_insert(int R, const Range &rg, const RadixWs &ws, unsigned char *lds) {
+// lk, lfirst, lcnt: [kAggSlots] mapped key (0: empty), first request (later the
+// slot), count.
+__device__ __forceinline__ void hash_insert(int R, const Range &rg, const RadixWs &ws,
+                                            unsigned long long *lk, int32_t *lfirst,
+                                            int32_t *lcnt) {
   constexpr int per = kAggRound / kRadixThreads;
-  unsigned long long *lk = (unsigned long long *)lds;   // mapped key (0: empty)
-  int32_t *lfirst = (int32_t *)(lds + 8 * kAggSlots);   // first request; later the slot
-  int32_t *lcnt = lfirst + kAggSlots;
   __shared__ int32_t zfirst, zcnt;               // the key that maps to 0
-  const int tid = threadIdx.x, hbits = ws.hbits;
+  const int tid = threadIdx.x, hbits = ws.hbits, shift = bucket_shift(rg.span, hbits);
   const uint32_t hmask = (1u << hbits) - 1u;
   constexpr int lbits = 11;
   static_assert((1 << lbits) == kAggSlots, "LDS table");
@@ -782,7 +757,7 @@ __device__ void hash_insert(int R, const Range &rg, const RadixWs &ws, unsigned 
       atomicAdd(&ws.hcnt[slot], (uint32_t)cnt);
     };
     auto append = [&](uint64_t key, uint32_t slot) {
-      const uint32_t b = (uint32_t)((key - rg.mn) >> rg.hash_shift);
+      const uint32_t b = (uint32_t)((key - rg.mn) >> shift);
       const uint32_t at = atomicAdd(&ws.bcnt[b], 1u);
       if (at < (uint32_t)kBucketCap) {
         ws.bkey[(int64_t)b * kBucketCap + at] = key;
@@ -858,8 +833,9 @@ __device__ void hash_groups(int R, const RadixWs &ws, int64_t *__restrict__ uk,
 // entry goes to the value arrays with one atomic min and one atomic add.
 // Workgroup 0 also stores the path for the later launches.
 __global__ __launch_bounds__(kRadixThreads) void dense_mark_kernel(int R, int P, RadixWs ws) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[16 * kAggSlots];
-  int32_t *tkey = (int32_t *)lds, *tfirst = tkey + kAggSlots, *tcount = tfirst + kAggSlots;
+  __shared__ unsigned long long thash[kAggSlots];   // hash path: mapped keys
+  __shared__ int32_t tfirst[kAggSlots], tcount[kAggSlots];
+  int32_t *const tkey = (int32_t *)thash;           // dense path: key values
   const Range rg = range_of(R, P, ws);
   const int tid = threadIdx.x;
   if (blockIdx.x == 0 && tid == 0) {
@@ -868,11 +844,10 @@ __global__ __launch_bounds__(kRadixThreads) void dense_mark_kernel(int R, int P,
     ws.range[2] = rg.nv;
     ws.range[3] = (uint64_t)rg.hash;
   }
-  if (rg.hash) {
-    hash_insert(R, rg, ws, lds);
+  if (__builtin_expect(!rg.nv, 0)) {   // (the dense path's code follows without a jump)
+    if (rg.hash) hash_insert(R, rg, ws, thash, tfirst, tcount);
     return;
   }
-  if (!rg.nv) return;
   int32_t *first = (int32_t *)ws.keyB, *count = (int32_t *)ws.keyB + R;
   for (int64_t round = blockIdx.x; round * kAggRound < R; round += gridDim.x) {
     const int64_t base = round * kAggRound;
@@ -921,13 +896,13 @@ __global__ __launch_bounds__(kRadixThreads) void dense_groups_kernel(
     int32_t *__restrict__ cnt, int64_t *__restrict__ nu_out) {
   __shared__ uint32_t wsum[kRadixThreads / 64 + 1];
   __shared__ uint32_t s_vb, s_before;
-  if (ws.range[3]) {
-    hash_groups(R, ws, uk, fi, cnt, nu_out);
+  const uint64_t nv = ws.range[2], hash = ws.range[3];   // (read together)
+  if (__builtin_expect(!nv, 0)) {
+    if (hash) hash_groups(R, ws, uk, fi, cnt, nu_out);
     return;
   }
-  const uint64_t nv = ws.range[2];
   const uint64_t nvb = (nv + kDenseBlk - 1) / kDenseBlk;
-  if (!nv || blockIdx.x >= nvb) return;
+  if (blockIdx.x >= nvb) return;
   const int tid = threadIdx.x;
   if (tid == 0)
     s_vb = __hip_atomic_fetch_add(ws.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1000,8 +975,8 @@ __global__ __launch_bounds__(kRadixThreads) void dense_groups_kernel(
 // Request -> group.
 __global__ __launch_bounds__(256) void dense_inverse_kernel(int R, RadixWs ws,
                                                             int32_t *__restrict__ inv) {
-  const uint64_t nv = ws.range[2];
-  if (ws.range[3]) {   // hash path
+  const uint64_t nv = ws.range[2], hash = ws.range[3];
+  if (hash) {
     if (ws.ctl[kCtlFull]) return;
     for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < R; p += (int64_t)gridDim.x * 256)
       inv[p] = ws.hgid[ws.idxB[p]];
@@ -1332,7 +1307,9 @@ hipError_t launch_dedup(const int64_t *keys, int64_t R, int64_t *uk, int32_t *fi
   int Ri = (int)R;
   const int64_t chunks = (R + kPrepChunk - 1) / kPrepChunk;
   const int P = chunks < kPrepMax ? (int)chunks : kPrepMax;
-  hipLaunchKernelGGL(dedup_prep_kernel, dim3(P + (w.hbits ? 1 : 0)), dim3(kRadixThreads), 0, st, keys, Ri, w);
+  // (hash path: workgroups that look at the sample and clear the table)
+  const int E = !w.hbits ? 0 : 1 + (P / 2 < 32 ? 32 : P / 2);
+  hipLaunchKernelGGL(dedup_prep_kernel, dim3(P + E), dim3(kRadixThreads), 0, st, keys, Ri, P, w);
   int64_t rounds = (R + kAggRound - 1) / kAggRound;
   if (rounds > 4096) rounds = 4096;
   hipLaunchKernelGGL(dense_mark_kernel, dim3((unsigned)rounds), dim3(kRadixThreads), 0, st, Ri,

@@ -160,8 +160,10 @@ def test_clustered_wide_keys_cost_no_more_than_the_sort(R, kind):
 @pytest.mark.parametrize("R", [600, 1_500, 2_048, 2_049, 4_096])
 @pytest.mark.parametrize("kind", ["sentinel", "2 tenants", "64 tenants", "powers"])
 def test_one_workgroup_ranking_of_clustered_keys(R, kind):
-    # keys that lie in few buckets of their range are ranked in about the time of
-    # uniform ones (4 to 65 times it while a bucket's keys were all compared)
+    # keys that lie in few buckets of their range are ranked in at most 2.1 times the
+    # time of uniform ones (choosing other buckets costs 6 us at 600 keys, 24 at 4,096);
+    # while a bucket's keys were all compared it was 3.9 to 65 times.  The line: 3 times
+    # and 3 us (one or two clusters; 64 of them are within it either way)
     note(f"dedup {kind} R={R}")
     rng = np.random.default_rng(R + len(kind))
     keys = rng.permutation(R)
@@ -176,4 +178,4 @@ def test_one_workgroup_ranking_of_clustered_keys(R, kind):
     _check(keys)
     _check(keys[rng.integers(0, keys.size, size=R)], runs=1)
     t, uniform = _time(keys), _time(_uniform(rng, R))
-    assert t < 2 * uniform + 0.005, f"{t * 1e3:.1f} us, uniform keys {uniform * 1e3:.1f} us"
+    assert t < 3 * uniform + 0.003, f"{t * 1e3:.1f} us, uniform keys {uniform * 1e3:.1f} us"
