@@ -888,22 +888,52 @@ def cpu_baseline(w, n_u: int, n_sample: int, threads_req: int = 0) -> dict:
             "measured_s": round(t_dedup + t_score, 2)}
 
 
-# The dedup path hs_dedup takes for a window's keys (the rule documented with
-# hs_dedup): one workgroup up to 4,096 requests (hash table up to 2,048), then
-# direct addressing when max - min < R, else an LSD radix sort with one pass
-# per 8 bits of max - min.
+# Which path hs_dedup takes for these keys (the rule of its kernels): one workgroup
+# up to 4,096 requests; above, direct addressing when max - min < R; a hash table in
+# the workspace (R <= 2^20) where the first 1,024 keys lie R or more apart, their
+# pairs in one bucket of the range leave room in the buckets, their searches in a
+# table of 2,048 slots are short and the whole range is less than twice theirs; else
+# an LSD radix sort with one pass per 8 bits of max - min.  The sort also follows a
+# table that was given up because a bucket got more than 1,024 distinct keys.
 def dedup_path(keys) -> str:
     import numpy as np
     R = int(keys.shape[0])
-    if R <= 2048:
-        return "lds-hash (one workgroup)"
     if R <= 4096:
-        return "bitonic (one workgroup)"
-    span = int(np.max(keys)) - int(np.min(keys))
+        return "lds-hash (one workgroup)"
+    m = np.asarray(keys, dtype=np.int64).view(np.uint64) ^ np.uint64(1 << 63)
+    low = int(m.min())
+    span = int(m.max()) - low
     if span < R:
         return f"direct addressing (key range {span + 1})"
-    passes = max(1, (span.bit_length() + 7) // 8)
-    return f"radix ({passes} passes of 8 bits)"
+    radix = f"radix ({(span.bit_length() + 7) // 8} passes of 8 bits)"
+    if R > 1 << 20:
+        return radix
+    bits = max(13, (2 * R - 1).bit_length())     # slots of the table
+
+    def per_bucket(distinct, first, width):
+        shift = np.uint64(max(0, width.bit_length() - (bits - 9)))
+        return np.bincount(((distinct - np.uint64(first)) >> shift).astype(np.int64))
+
+    sample = m[:1024]
+    first, width = int(sample.min()), int(sample.max()) - int(sample.min())
+    if width < R or span >> 1 > width:
+        return radix
+    distinct = np.unique(sample[sample != 0])
+    n = per_bucket(distinct, first, width)
+    if R * int((n * (n - 1)).sum()) > 768 * 1024 * distinct.size:
+        return radix
+    taken = set()
+    for k in distinct.tolist():
+        slot = (k * 0x9E3779B97F4A7C15 & (1 << 64) - 1) >> 53
+        steps = 1
+        while slot in taken:
+            slot, steps = (slot + 1) % 2048, steps + 1
+        taken.add(slot)
+        if steps > 128:
+            return radix
+    if per_bucket(np.unique(m), low, span).max() > 1024:
+        return f"hash table given up, then {radix}"
+    return "hash table in the workspace"
 
 
 if __name__ == "__main__":

@@ -33,10 +33,25 @@ def test_host_side_helpers():
     import numpy as np
     import bench
     assert bench.dedup_path(np.arange(100, dtype=np.int64)).startswith("lds-hash")
-    assert bench.dedup_path(np.arange(3000, dtype=np.int64)).startswith("bitonic")
+    assert bench.dedup_path(np.arange(4096, dtype=np.int64)).startswith("lds-hash")
     assert bench.dedup_path(np.arange(10000, dtype=np.int64) % 5000).startswith("direct")
-    big = np.array([0, 1 << 40] * 5000, dtype=np.int64)
+    big = np.array([0, 1 << 40] * 5000, dtype=np.int64)      # two keys, far apart
+    assert bench.dedup_path(big) == "hash table in the workspace"
+    big[:1024] = 0                                           # not seen in the sample
     assert bench.dedup_path(big) == "radix (6 passes of 8 bits)"
+    rng = np.random.default_rng(1)
+    wide = rng.integers(-(1 << 63), (1 << 63) - 1, size=40_000, endpoint=True)
+    assert bench.dedup_path(wide) == "hash table in the workspace"
+    assert bench.dedup_path(np.r_[wide[:1024] >> 20, wide]) == "radix (8 passes of 8 bits)"
+    assert bench.dedup_path(np.resize(wide, (1 << 20) + 1)) == "radix (8 passes of 8 bits)"
+    ids = np.r_[np.arange(39_999), [(1 << 63) - 1]][::-1].copy()   # dense ids and a sentinel
+    assert bench.dedup_path(ids) == "radix (8 passes of 8 bits)"
+    near = rng.random(40_000) < 0.05                         # 2,000 keys in one bucket
+    part = np.where(near, np.arange(40_000), wide)
+    assert bench.dedup_path(part) == "hash table given up, then radix (8 passes of 8 bits)"
+    inv = pow(0x9E3779B97F4A7C15, -1, 1 << 64)               # hashes that all begin at slot 0
+    same = (np.arange(1, 40_001, dtype=np.uint64) * np.uint64(inv)) ^ np.uint64(1 << 63)
+    assert bench.dedup_path(same.view(np.int64)).startswith("radix")
     assert bench.oracle_threads(7) == 7
     assert bench.oracle_threads(0) >= 1
     info = bench.host_cpu()
