@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import bench
 import synth
 from gpu_harness import device, note
 
@@ -14,13 +15,22 @@ I64_MIN = np.iinfo(np.int64).min
 I64_MAX = np.iinfo(np.int64).max
 
 
-def _gpu_dedup(keys, host_count=False):
+def _for_the_sort(keys):
+    """The same keys behind 1,024 requests of one key: wide keys that the hash path
+    does not take, whatever their distribution."""
+    keys = np.r_[np.full(1_024, keys[0], dtype=np.int64), keys[:-1_024]]
+    assert bench.dedup_path(keys).startswith("radix"), bench.dedup_path(keys)
+    return keys
+
+
+def _gpu_dedup(keys, host_count=False, ws=None):
     import paper_2607_22578_amd as hs
     import oracle
     dev = device()
     R = keys.shape[0]
     plan = hs.hs_merge_plan(R, 8, 1, 1, hs.HS_BF16, hs.HS_BF16)
-    ws = torch.empty(max(plan.workspace_bytes, 256), dtype=torch.uint8, device=dev)
+    if ws is None:
+        ws = torch.empty(max(plan.workspace_bytes, 256), dtype=torch.uint8, device=dev)
     R1 = max(R, 1)
     kd = torch.from_numpy(keys.astype(np.int64)).to(dev) if R else None
     uk = torch.full((R1,), 7, dtype=torch.int64, device=dev)
@@ -59,7 +69,9 @@ def test_dedup_workload_keys(name):
                                   "dense_span_r_minus_1", "radix_span_r", "dense_negative",
                                   "dense_hot_zipf"])
 def test_dedup_edge_cases(case):
-    # paths: hash table up to 2,048 keys, bitonic sort up to 4,096, radix sort
+    # paths: one workgroup up to 4,096 keys (its table has two sizes, up to 2,048 and
+    # above); above, direct addressing, the workspace's hash table or the radix sort
+    # ("radix" cases with a wide range run through both)
     rng = np.random.default_rng(zlib.crc32(case.encode()))
     if case == "one":
         keys = np.array([12345], np.int64)
@@ -112,6 +124,9 @@ def test_dedup_edge_cases(case):
         keys = rng.integers(0, 300, size=20_000).astype(np.int64)
         keys[12345] = I64_MIN
     _gpu_dedup(keys)
+    if case.endswith("radix") and int(keys.max()) - int(keys.min()) >= keys.size:
+        assert bench.dedup_path(keys).startswith("hash table")
+        _gpu_dedup(_for_the_sort(keys))
 
 
 def test_dedup_empty():
@@ -139,34 +154,54 @@ def test_dedup_more_tiles_than_workgroups(case):
     else:
         keys = rng.integers(0, 1 << 40, size=R).astype(np.int64)
         keys[rng.random(R) < 0.3] = 17   # a hot key
+        assert bench.dedup_path(keys).startswith("radix")
     note(f"dedup {case} R={R}")
     _gpu_dedup(keys)
 
 
-@pytest.mark.parametrize("tiles", [64, 65, 257])
-def test_radix_digit_offsets_around_the_tile_threshold(tiles):
+@pytest.mark.parametrize("kind", ["wide", "2 tenants"])
+@pytest.mark.parametrize("tiles", [64, 65, 100, 256, 257])
+def test_radix_digit_offsets_around_the_tile_threshold(tiles, kind):
     # the sort takes its digit offsets straight from the histogram up to 64
     # tiles of 4,096 keys and from per-digit row scans above; 257 tiles is
     # more than the persistent sort's 256 workgroups (one takes two tiles);
     # ragged last tile, hot keys, negative keys
     rng = np.random.default_rng(100 + tiles)
     R = tiles * 4096 - 1000
-    keys = rng.integers(-(1 << 62), 1 << 62, size=R).astype(np.int64)
-    keys[rng.random(R) < 0.2] = -5
-    keys[rng.random(R) < 0.1] = 1 << 61
+    if kind == "wide":
+        keys = rng.integers(-(1 << 62), 1 << 62, size=R).astype(np.int64)
+        keys[rng.random(R) < 0.2] = -5
+        keys[rng.random(R) < 0.1] = 1 << 61
+        keys = _for_the_sort(keys)
+    else:                    # two clusters: sorted without an attempt on the table
+        keys = (rng.integers(0, R, size=R) + (rng.integers(0, 2, size=R) << 40)).astype(np.int64)
+        assert bench.dedup_path(keys).startswith("radix")
     note(f"dedup radix R={R} ({tiles} tiles)")
     _gpu_dedup(keys)
 
 
-def test_dense_and_sort_paths_alternate_on_one_workspace():
-    # the same plan and workspace for a dense-range batch, then a sort-path
-    # batch, then dense again: every launch resets the scratch it needs
-    rng = np.random.default_rng(77)
-    R = 40_000
+@pytest.mark.parametrize("tiles", [10, 64, 65, 100])
+def test_dense_hash_and_sort_paths_alternate_on_one_workspace(tiles):
+    # one workspace for every path after every other: each launch resets the scratch
+    # it needs.  "given up": 8 % of the keys (3 % at 65 tiles and more) in one bucket,
+    # which the sample does not tell and the marking finds full
+    import paper_2607_22578_amd as hs
+    rng = np.random.default_rng(77 + tiles)
+    R = tiles * 4096 - 55
     dense = rng.integers(0, R // 2, size=R).astype(np.int64)
-    wide = rng.integers(-(1 << 40), 1 << 40, size=R).astype(np.int64)
-    for k in (dense, wide, dense, wide):
-        _gpu_dedup(k)
+    wide = rng.integers(-(1 << 62), 1 << 62, size=R).astype(np.int64)
+    full = np.where(rng.random(R) < (0.08 if tiles < 64 else 0.03), np.arange(R), wide)
+    batches = {"direct": dense, "hash table in": wide, "hash table given up": full,
+               "radix": _for_the_sort(wide)}
+    for path, keys in batches.items():
+        assert bench.dedup_path(keys).startswith(path), (path, bench.dedup_path(keys))
+    ws = torch.full((hs.hs_merge_plan(R, 8, 1, 1, hs.HS_BF16, hs.HS_BF16).workspace_bytes,), 0xA5,
+                    dtype=torch.uint8, device=device())
+    order = ["direct", "hash table in", "direct", "hash table given up", "hash table in", "radix",
+             "hash table given up", "direct", "radix", "hash table in", "hash table in"]
+    for path in order:
+        note(f"dedup {path} R={R}")
+        _gpu_dedup(batches[path], ws=ws)
 
 
 def test_sort_path_beside_a_concurrent_score_call():
@@ -193,6 +228,7 @@ def test_sort_path_beside_a_concurrent_score_call():
     R = 300_000
     keys = rng.integers(-(1 << 50), 1 << 50, size=R).astype(np.int64)
     keys[rng.random(R) < 0.25] = 12345
+    keys = _for_the_sort(keys)
     ref = oracle.dedup(keys)
     plan = hs.hs_merge_plan(R, 8, 1, 1, hs.HS_BF16, hs.HS_BF16)
     ws = torch.empty(max(plan.workspace_bytes, 256), dtype=torch.uint8, device=dev)

@@ -1,11 +1,12 @@
 """Dedup of wide-range keys through the hash table, and its edges: the smallest
 and largest request counts of the path, the key that maps to the empty mark
-(INT64_MIN), hot keys, keys that fill one bucket (left to the sort) and keys
-whose first 1,024 lie close together (never hashed)."""
+(INT64_MIN), hot keys, keys in few buckets and keys whose first 1,024 lie close
+together (left to the sort).  The one-workgroup table's ranking."""
 import numpy as np
 import pytest
 import torch
 
+import bench
 import oracle
 from gpu_harness import device, note, to_dev
 
@@ -61,9 +62,9 @@ def test_extreme_keys_and_hot_keys():
 
 @pytest.mark.parametrize("kind", ["clustered", "few outliers", "late range", "all equal but one"])
 def test_keys_the_table_does_not_suit(kind):
-    # clustered: two runs of consecutive keys far apart fill two buckets, so
-    # the hash path gives up and the sort runs; late range: the first 1,024
-    # keys are close together, so the sort runs at once
+    # clustered: two runs of consecutive keys far apart would fill two buckets; few
+    # outliers: most keys in one; late range: the first 1,024 keys are close together:
+    # the sort runs at once
     rng = np.random.default_rng(6)
     n = 20_000
     if kind == "clustered":
@@ -77,7 +78,10 @@ def test_keys_the_table_does_not_suit(kind):
     else:
         keys = np.full(n, 3, dtype=np.int64)
         keys[0] = I64.max
-    _check(keys.astype(np.int64))
+    keys = keys.astype(np.int64)
+    want = "hash table" if kind == "all equal but one" else "radix"
+    assert bench.dedup_path(keys).startswith(want), bench.dedup_path(keys)
+    _check(keys)
 
 
 @pytest.mark.parametrize("R", [513, 600, 2_047, 2_048, 2_049, 3_000, 4_096])
