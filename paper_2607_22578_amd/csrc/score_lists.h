@@ -94,11 +94,6 @@ __device__ __forceinline__ i32x4m make_rsrc(const void *base, uint32_t bytes) {
 // here is harmless.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(i32x4m rsrc, const void *lds, uint32_t voff) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(l), "v"(voff), "s"(rsrc) : "memory", "m0");
-}
 __device__ __forceinline__ void dma4(i32x4m rsrc, const void *lds, uint32_t voff) {
   const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"

@@ -285,32 +285,9 @@ __device__ __forceinline__ void pin_step1(Frag<FP8, NQB> &f) {
   for (int qb = 0; qb < NQB; ++qb) pin_u4(f.b[1][qb]);
 }
 
-// One 16-deep MFMA step over the wave's kMRB x NQB blocks.
-template <bool FP8, bool ZERO, int NQB>
-__device__ __forceinline__ void mfma_step(f32x16m (&acc)[kMRB][NQB], const Frag<FP8, NQB> &f,
-                                          int s) {
-  bf16x8m av[kMRB];
-#pragma unroll
-  for (int rb = 0; rb < kMRB; ++rb) {
-    if constexpr (FP8) {
-      const uint4 v = f.a[0][rb];
-      if (s == 0) cvt8_fp8_bf16(v.x, v.y, av[rb]);
-      else cvt8_fp8_bf16(v.z, v.w, av[rb]);
-    } else {
-      av[rb] = __builtin_bit_cast(bf16x8m, f.a[s][rb]);
-    }
-  }
-  const f32x16m zero = {};
-#pragma unroll
-  for (int rb = 0; rb < kMRB; ++rb)
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
-      acc[rb][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-          av[rb], __builtin_bit_cast(bf16x8m, f.b[s][qb]), ZERO ? zero : acc[rb][qb], 0, 0, 0);
-}
-
-// The same with op(i) issued after the i-th matrix instruction, in its shadow
-// (a scheduling barrier after each keeps the order).
+// One 16-deep MFMA step over the wave's kMRB x NQB blocks, with op(i) issued after
+// the i-th matrix instruction, in its shadow (a scheduling barrier after each keeps
+// the order).
 template <bool FP8, bool ZERO, int NQB, typename Op>
 __device__ __forceinline__ void mfma_step_il(f32x16m (&acc)[kMRB][NQB], const Frag<FP8, NQB> &f,
                                              int s, Op &&op) {
@@ -529,6 +506,7 @@ __device__ __forceinline__ void merge_any(const MLds &L, const MfmaArgs &a, cons
                                           const uint32_t *gt) {
   constexpr int QC = kQcap<kWaveLists>;
   static_assert(QC <= 32 && QC % 8 == 0, "a key per lane of half a wave, read by eights");
+  static_assert(QC <= kTailMax, "these lists are longer than a queue");
   const int tid = opaque(threadIdx.x), lane = tid & 63, wv = tid >> 6, e = lane & 31;
   const int mine = wv + kMW * e;
   if (__builtin_amdgcn_ballot_w64(mine < it.qvalid && L.lmin[mine] != 0ull)) {
@@ -555,16 +533,10 @@ __device__ __forceinline__ void merge_any(const MLds &L, const MfmaArgs &a, cons
     }
     const uint64_t mask = __builtin_amdgcn_ballot_w64(x != 0ull);
     const int live = __builtin_popcount((uint32_t)(lane < 32 ? mask : mask >> 32));
-    if (x != 0ull && pos < a.k) {
-      a.part[((int64_t)(it.qbase + q) * it.S + it.s) * a.k + pos] = x;
-      const float sc = unord_score((uint32_t)(x >> 32));
-      if (pos == a.k - 1 && sc > th) {
-        L.thr[q] = sc;
-        publish_thr(L, a, it, q, sc);
-      }
-    }
+    // (fewer keys than k: no threshold yet)
+    if (x != 0ull) a.part[((int64_t)(it.qbase + q) * it.S + it.s) * a.k + pos] = x;
     if (e == 0 && n > 0) {
-      L.lmin[q] = (uint64_t)(live < a.k ? live : a.k);
+      L.lmin[q] = (uint64_t)live;
       L.qcount[q] = 0;
     }
   }
@@ -610,6 +582,22 @@ __device__ __forceinline__ void pin_acc(f32x16m (&acc)[kMRB][NQB]) {
     for (int qb = 0; qb < NQB; ++qb) asm volatile("" : "+a"(acc[rb][qb]));
 }
 
+// NaN for the scores of rows past N (only for a tile that reaches past N).
+template <int NQB>
+__device__ __forceinline__ void mask_tail(f32x16m (&acc)[kMRB][NQB], int lim0) {
+  if (lim0 < 32 * kMRB) {   // some of this lane's rows are past N
+    const float nan = __builtin_nanf("");
+#pragma unroll
+    for (int rb = 0; rb < kMRB; ++rb)
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (rb * 32 + 8 * (i >> 2) + (i & 3) >= lim0) acc[rb][qb][i] = nan;
+    pin_acc(acc);
+  }
+}
+
 // Turns the tile's accumulators into scores in place, once per tile: the fp8
 // row scale applied, NaN for rows past N (NaN fails every >= test and fmaxf
 // ignores it).  Accumulator element (rb, qb, i) of a lane is row
@@ -637,32 +625,7 @@ __device__ __forceinline__ void finish_scores(f32x16m (&acc)[kMRB][NQB], const f
         }
       }
   }
-  if (lim0 < 32 * kMRB) {   // some of this lane's rows are past N
-    const float nan = __builtin_nanf("");
-#pragma unroll
-    for (int rb = 0; rb < kMRB; ++rb)
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (rb * 32 + 8 * (i >> 2) + (i & 3) >= lim0) acc[rb][qb][i] = nan;
-    pin_acc(acc);
-  }
-}
-// NaN for the scores of rows past N (only for a tile that reaches past N).
-template <int NQB>
-__device__ __forceinline__ void mask_tail(f32x16m (&acc)[kMRB][NQB], int lim0) {
-  if (lim0 < 32 * kMRB) {   // some of this lane's rows are past N
-    const float nan = __builtin_nanf("");
-#pragma unroll
-    for (int rb = 0; rb < kMRB; ++rb)
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (rb * 32 + 8 * (i >> 2) + (i & 3) >= lim0) acc[rb][qb][i] = nan;
-    pin_acc(acc);
-  }
+  mask_tail(acc, lim0);
 }
 
 // The 16 fp8 row scales of row block rb of this lane (rows rb * 32 + 8 * (i /
