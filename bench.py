@@ -21,9 +21,10 @@ from __future__ import annotations
 
 import argparse
 import hashlib
-import re
 import json
+import math
 import os
+import re
 import sys
 import time
 
@@ -891,7 +892,7 @@ def cpu_baseline(w, n_u: int, n_sample: int, threads_req: int = 0) -> dict:
 # Which path hs_dedup takes for these keys (the rule of its kernels): one workgroup
 # up to 4,096 requests; above, direct addressing when max - min < R; a hash table in
 # the workspace (R <= 2^20) where the first 1,024 keys lie R or more apart, their
-# pairs in one bucket of the range leave room in the buckets, their searches in a
+# numbers in the buckets of the range leave room there, their searches in a
 # table of 2,048 slots are short and the whole range is less than twice theirs; else
 # an LSD radix sort with one pass per 8 bits of max - min.  The sort also follows a
 # table that was given up because a bucket got more than 1,024 distinct keys.
@@ -920,7 +921,9 @@ def dedup_path(keys) -> str:
         return radix
     distinct = np.unique(sample[sample != 0])
     n = per_bucket(distinct, first, width)
-    if R * int((n * (n - 1)).sum()) > 768 * 1024 * distinct.size:
+    t = (1 << 20) // R
+    if n.max() > t + 4 * math.isqrt(t) + 4 or \
+            R * int((n * (n - 1)).sum()) > 768 * 1024 * distinct.size:
         return radix
     taken = set()
     for k in distinct.tolist():

@@ -449,7 +449,12 @@ __device__ __forceinline__ uint32_t hash_of(uint64_t m, int bits) {
 // keys that share a random key's bucket are about D p / n^2 of D distinct ones,
 // and D is at most R n / 1024 (new keys get rarer).  Signatures have 512 at most
 // (twice R / buckets, half of the buckets used) with a deviation of 32; the limit
-// lies between that and the bucket's size.  A search of more than 128 slots here
+// lies between that and the bucket's size.  One crowded bucket among many weighs
+// little in that mean: t = 2^20 / R keys of the sample in one bucket stand for the
+// 1,024 that it holds, and t + 4 sqrt(t) + 4 are not there by chance.  5,000 keys,
+// 30 % of them within one bucket: 268 us with an attempt, 232 without.  What gets
+// past both costs the attempt: 1 % of 200,000 keys in one bucket 526 us (the sort
+// alone 441), of 10^6 1,874 (1,359), 2 % of 65,536 333 (280).  A search of more than 128 slots here
 // (36 are usual for 1,024 keys in 2,048 slots) tells keys that the hash does not
 // spread.
 constexpr uint64_t kSpreadMax = 768;
@@ -466,7 +471,7 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
   __shared__ unsigned long long set[slots];
   __shared__ uint32_t cnt[kBucketsMax];
   __shared__ uint64_t smin[W], smax[W];
-  __shared__ uint32_t total, longer;   // distinct keys << 21 | pairs (< 2^20); a search too long
+  __shared__ uint32_t total, unfit;   // distinct keys << 21 | pairs (< 2^20)
   const int tid = threadIdx.x;
   uint64_t m[per], mn = ~0ull, mx = 0ull;
 #pragma unroll
@@ -478,7 +483,7 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
   if (e0 == 0) {
     for (int i = tid; i < slots; i += kRadixThreads) set[i] = 0ull;
     for (int i = tid; i < 1 << bucket_bits(ws.hbits); i += kRadixThreads) cnt[i] = 0u;
-    if (tid == 0) total = longer = 0u;
+    if (tid == 0) total = unfit = 0u;
   }
   for (int o = 32; o > 0; o >>= 1) {
     const uint64_t a = __shfl_xor(mn, o, 64), c = __shfl_xor(mx, o, 64);
@@ -510,6 +515,7 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
     return;
   }
   const int shift = bucket_shift(span, ws.hbits);
+  const uint32_t t = (1u << 20) / (uint32_t)R, crowd = t + 4u * (uint32_t)sqrtf((float)t) + 4u;
   // (the four keys' first steps are in flight together; 0, the mark of an empty
   // slot, is one key at most and is not counted)
   uint32_t h[per], sum = 0u;
@@ -526,18 +532,21 @@ __device__ void sample_spread(const int64_t *__restrict__ keys, int R, const Rad
       h[e] = (h[e] + 1) & (slots - 1);
       prev[e] = atomicCAS(&set[h[e]], 0ull, m[e]);
     }
-    if (left == 0) longer = 1u;
+    if (left == 0) unfit = 1u;
   }
 #pragma unroll
   for (int e = 0; e < per; ++e)
-    if (prev[e] == 0ull && m[e] != 0ull)
-      sum += (1u << 21) + 2u * atomicAdd(&cnt[(uint32_t)((m[e] - mn) >> shift)], 1u);
+    if (prev[e] == 0ull && m[e] != 0ull) {
+      const uint32_t others = atomicAdd(&cnt[(uint32_t)((m[e] - mn) >> shift)], 1u);
+      sum += (1u << 21) + 2u * others;
+      if (others >= crowd) unfit = 1u;
+    }
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
   if ((tid & 63) == 0) atomicAdd(&total, sum);
   __syncthreads();
   if (tid == 0) {
     const uint64_t n = total >> 21, pairs = total & ((1u << 21) - 1u);
-    const bool fit = longer == 0u && (uint64_t)R * pairs <= kSpreadMax * kSampleKeys * n;
+    const bool fit = unfit == 0u && (uint64_t)R * pairs <= kSpreadMax * kSampleKeys * n;
     ws.range[4] = fit ? span : 0ull;
   }
 }
@@ -897,8 +906,8 @@ __global__ __launch_bounds__(kRadixThreads) void dense_groups_kernel(
   __shared__ uint32_t wsum[kRadixThreads / 64 + 1];
   __shared__ uint32_t s_vb, s_before;
   const uint64_t nv = ws.range[2], hash = ws.range[3];   // (read together)
-  if (__builtin_expect(!nv, 0)) {
-    if (hash) hash_groups(R, ws, uk, fi, cnt, nu_out);
+  if (hash) {
+    hash_groups(R, ws, uk, fi, cnt, nu_out);
     return;
   }
   const uint64_t nvb = (nv + kDenseBlk - 1) / kDenseBlk;

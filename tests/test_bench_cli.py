@@ -46,9 +46,12 @@ def test_host_side_helpers():
     assert bench.dedup_path(np.resize(wide, (1 << 20) + 1)) == "radix (8 passes of 8 bits)"
     ids = np.r_[np.arange(39_999), [(1 << 63) - 1]][::-1].copy()   # dense ids and a sentinel
     assert bench.dedup_path(ids) == "radix (8 passes of 8 bits)"
-    near = rng.random(40_000) < 0.05                         # 2,000 keys in one bucket
+    near = rng.random(40_000) < 0.035                        # 1,400 keys in one bucket
     part = np.where(near, np.arange(40_000), wide)
     assert bench.dedup_path(part) == "hash table given up, then radix (8 passes of 8 bits)"
+    near = rng.random(40_000) < 0.1
+    part = np.where(near, np.arange(40_000), wide)
+    assert bench.dedup_path(part) == "radix (8 passes of 8 bits)"
     inv = pow(0x9E3779B97F4A7C15, -1, 1 << 64)               # hashes that all begin at slot 0
     same = (np.arange(1, 40_001, dtype=np.uint64) * np.uint64(inv)) ^ np.uint64(1 << 63)
     assert bench.dedup_path(same.view(np.int64)).startswith("radix")
