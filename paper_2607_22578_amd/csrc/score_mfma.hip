@@ -164,10 +164,16 @@ struct Geo {
 // Long items with kWaveLists also publish, and raise their queries' thresholds,
 // while they run: after kLvlFirst tiles and whenever that number has doubled.
 // Slices that run at the same time then share one bound instead of each filling
-// a list of its own: 20M fp8 rows run as 14 slices of 3,720 tiles, all at once,
-// and queued 304 keys per query and slice before, 85 with it (68.9 -> 65.4 ms).
+// a list of its own.  A raise reads 5 S words per query, so where items follow in
+// later rounds anyway, and start from what the finished slices published, it is
+// done only for up to kLvlSlices slices.  Without -> with it, k = 100 unless said:
+// 20M x 768 fp8, 2,100 queries (15 slices of 3,472 tiles, one round) 69.2 -> 64.7
+// ms, but 2,190 queries (71 slices of 733, five rounds) 70.7 -> 72.1; 5M fp8, 3,000
+// queries (32 slices, three rounds) 25.4 -> 25.0, 9,000 (18, five) 74.1 -> 73.4;
+// k = 40, 1,100 queries (142, five) 9.4 -> 9.8; 4M x 512 bf16, k = 64, 2,190
+// queries (71, five) 10.7 -> 11.6.
 constexpr int kLvl = 5;
-constexpr int kLvlFirst = 32;
+constexpr int kLvlFirst = 32, kLvlSlices = 48;
 constexpr int kMWarmBytes = kMW * kMMQ * 4;   // per-wave warm-up minima (alias the queue)
 static_assert(kMWarmBytes <= kMMQ * kMQcap * 8, "warm-up minima fit in the queue");
 
@@ -1154,7 +1160,10 @@ __device__ __forceinline__ void run_item(const MfmaArgs &a, const MLds &L, const
     // last stage of a tile leaves the next fragments in LDS: the epilogue runs
     // with only the accumulators live, and f0 is refilled after it.)
     const bool later = sp.qtiles * sp.S > a.grid;   // there are items that start later
-    int due = it.S > 1 ? kLvlFirst : 0;   // tiles done at the next publication
+    // tiles done at the next publication (none: more than any slice has; 0 for none,
+    // in one expression, took 8 more scalar spills and 1 % of 500,009 fp8 rows)
+    int due = kLvlFirst;
+    if (sp.S == 1 || (later && sp.S > kLvlSlices)) due = 1 << 29;
     for (int tl = 0; tl < ntl; ++tl) {
       if (nch > 1) {
         stage(std::true_type{}, std::true_type{});
