@@ -34,7 +34,7 @@ sys.path.insert(0, ROOT)
 METRIC = "merged retrieval queries/s + achieved HBM GB/s or MFMA % (dedup+score+top-k)"
 PEAK_HBM_GBS = 8000.0
 PEAK_MFMA = {"bf16": 2500.0}          # dense TFLOP/s (no sparsity)
-PEAK_FP32_VECTOR = 157.3              # TFLOP/s, fp32 on the vector units
+PEAK_FP32_VECTOR = 157.3              # TFLOP/s, fp32 (vector and matrix units alike)
 DEFAULT_WORKLOAD = "mfma4m"
 
 

@@ -142,8 +142,8 @@ hs_status hs_workflow_rows(const hs_plan *plan, int64_t w, int64_t *first, int64
  * Method (for any int64 keys; the outputs do not depend on it): one workgroup
  * with an LDS hash table for R <= 4,096; above, the key range is found on the
  * device and the keys are numbered by direct addressing when max - min < R,
- * else (R <= 2^20, keys spread over the range) grouped by a hash table in the
- * workspace, else sorted by an LSD radix sort with one pass per 8 bits of
+ * else (R <= 2^20, keys spread evenly over the range as a sample of them tells)
+ * grouped by a hash table in the workspace, else sorted by an LSD radix sort with one pass per 8 bits of
  * max - min. */
 hs_status hs_dedup(const hs_plan *plan, const int64_t *keys, int64_t *unique_keys,
                    int32_t *first_index, int32_t *counts, int32_t *inverse,

@@ -350,10 +350,11 @@ struct RadixWs {
 // three grid barriers: 410 us for 200,000 of them, of which the bytes are 5.
 // (200,000 signatures, 95,000 distinct: marking 52 us, groups 8 us.)  The table
 // has at least 2 R slots; with R rounded up to a power of two there
-// is a bucket of the key range per 256 requests, so that uniform keys (the
-// signatures are hash values) fill a bucket to at most 256 on average, and
-// never to kBucketCap.  Keys that do are left to the sort.  Up to 2^20
-// requests: the table and the buckets take 90 bytes per request or more.
+// is a bucket of the key range per 256 requests.  Uniform keys (the signatures
+// are hash values) fill a bucket to at most 256 on average over the full range
+// of 64 bits, and to at most 512 over a range just above a power of two (half of
+// the buckets used), never to kBucketCap.  Keys that do are left to the sort.  Up
+// to 2^20 requests: the table and the buckets take 90 bytes per request or more.
 //
 // A key's search in the table ends after kProbeMax slots.  In a table that is at
 // most half full the longest search is about ln(R) / 0.19 slots (72 for 2^20 keys),

@@ -405,7 +405,8 @@ __device__ __forceinline__ int opaque(int x) {
 // One thread per query inserted its keys one after the other before, climbing
 // the list in windows of 8 dependent global reads, and the wave took as long as
 // its longest thread: 174,000 cycles per round of merges, 12.5 % of the main
-// pass over 20M fp8 rows, k = 100, with queues of 8.
+// pass over 20M fp8 rows, k = 100, with queues of 8 (the shader clock read around
+// the rounds in a copy of the kernel).
 __device__ __forceinline__ uint64_t lane_key(uint64_t x, int f) {
   const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)x, f);
   const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), f);
